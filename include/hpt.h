@@ -274,10 +274,11 @@ hpt_status hpt_ctx_stats_get(hpt_ctx *ctx, hpt_ctx_stats *out);
  *     re, im), row-major; may be the same buffer. Caller-owned.
  *   width, height: 1..4096; pitch, lambda > 0 (metres); distance finite.
  * hip_stream (nullable): the propagation starts after all work enqueued on
- * that stream before the call. Synchronous (returns when d_out is written). Scratch (two [height][P_x]
- * complex64 buffers per field of a chunk of fields, at most 1 GiB, and the
- * transforms' twiddle tables) is taken from the context's budget for the call. EINVAL on bad arguments, EBUDGET if
- * one field's scratch does not fit, EDEVICE on a HIP error. */
+ * that stream before the call. Synchronous (returns when d_out is written). Scratch (a [height][P_x]
+ * complex64 buffer per field of a chunk of fields, at most 160 MiB or one
+ * field's, and a quarter of the transfer function) is taken from the context's
+ * budget for the call. EINVAL on bad arguments, EBUDGET if one field's scratch
+ * does not fit, EDEVICE on a HIP error. */
 #define HPT_ASM_BAND_LIMIT 1u
 hpt_status hpt_asm_propagate(hpt_ctx *ctx, const void *d_in, void *d_out, uint32_t n_fields,
                              uint32_t width, uint32_t height, double pitch, double lambda,
@@ -288,7 +289,8 @@ hpt_status hpt_asm_propagate(hpt_ctx *ctx, const void *d_in, void *d_out, uint32
  * harnesses that forbid hipMalloc): it allocates nothing, host or device, and
  * its kernels (those of hpt_asm_propagate) work in a static scratch of
  * 9437184 complex64 (72 MiB) that each device holds from the library's first
- * context until the process ends. Limit: 2 height P_x + P_x + P_y <= 9437184
+ * context until the process ends (with the transforms' twiddle table, 256 KiB).
+ * Limit: 2 height P_x + P_x + P_y <= 9437184
  * (P_x, P_y: the padded sizes), e.g. one 1920 x 1080 field at a time; larger
  * fields return EINVAL. hip_stream non-null: the work is enqueued on that
  * stream and the call returns without waiting (d_out is ready in stream
@@ -316,11 +318,12 @@ hpt_status hpt_asm_propagate_noalloc(hpt_ctx *ctx, const void *d_in, void *d_out
  *     metres; lambdas > 0, distances finite; width, height: 1..4096;
  *     n_ch, T >= 1; 1 <= n_planes <= 64; na finite.
  * The forward transforms of a chunk of frames are computed once and reused
- * for every plane. hip_stream (nullable): starts after the work enqueued on
- * it before the call. Synchronous. Scratch (three [height][P_x] complex64
- * buffers per frame of a chunk, at most 1 GiB, and twiddle tables) from the
+ * for the planes. hip_stream (nullable): starts after the work enqueued on
+ * it before the call. Synchronous. Scratch (per frame of a chunk a
+ * [height][P_x] complex64 buffer and one more for each plane taken at a time,
+ * with a quarter of each plane's transfer function, at most 1 GiB) from the
  * context's budget for the call. EINVAL on bad arguments, EBUDGET if one
- * frame's scratch does not fit, EDEVICE on a HIP error. */
+ * frame's scratch for one plane does not fit, EDEVICE on a HIP error. */
 hpt_status hpt_reconstruct(hpt_ctx *ctx, const void *d_fields, uint32_t n_ch, uint32_t T, uint32_t width,
                            uint32_t height, double pitch, const double *lambdas, uint32_t n_planes,
                            const double *distances, double na, uint32_t flags, void *d_out,
@@ -346,10 +349,10 @@ hpt_status hpt_reconstruct(hpt_ctx *ctx, const void *d_fields, uint32_t n_ch, ui
  *   width, height 1..4096; pitch, lambda > 0; distance finite;
  *   iterations 0..100000; lr > 0.
  * hip_stream (nullable): starts after the work enqueued on it before the
- * call. Synchronous. Scratch (five [height][width] buffers and two [height][P_x]
- * complex64 buffers per field of a chunk, at most 1 GiB) from the
- * context's budget for the call. EINVAL, EBUDGET, EDEVICE as for
- * hpt_asm_propagate. */
+ * call. Synchronous. Scratch (24 bytes per pixel and a [height][P_x] complex64
+ * buffer per field of a chunk, at most 512 MiB or one field's, and a quarter of
+ * the transfer functions) from the context's budget for the call. EINVAL,
+ * EBUDGET, EDEVICE as for hpt_asm_propagate. */
 #define HPT_ENCODE_WARM_START 2u
 hpt_status hpt_encode_phase(hpt_ctx *ctx, const void *d_fields, uint32_t n_fields, uint32_t width,
                             uint32_t height, double pitch, double lambda, double distance,

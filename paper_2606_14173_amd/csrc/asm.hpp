@@ -1,8 +1,9 @@
-// Angular-spectrum propagation launcher (second stage of the two-stage
+// Angular-spectrum propagation launchers (second stage of the two-stage
 // scheme, Sec. 4.4).
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
 #include <cstdint>
 
 namespace hpt {
@@ -18,37 +19,43 @@ struct AsmParams {
   uint32_t band_limit;
 };
 
-// Padded length of one axis: the next power of two >= 2 n.
+// Padded length of one axis: the next power of two >= 2 n (1 <= n <= 4096).
 uint32_t asm_padded(uint32_t n);
 
 // Complex64 elements of the static scratch of the allocation-free
 // propagation (72 MiB: one 1920 x 1080 field, padded to 4096 columns, with
-// its two work buffers and the twiddle tables).
+// its work buffer and its transfer function).
 constexpr size_t kNoAllocScratchElems = 9437184;
-// Device address of that scratch on `device` (which must be current): taken
-// once per device with hipGetSymbolAddress and kept for the process.
-hipError_t asm_noalloc_scratch(int device, float2 **ptr);
+// Device addresses of what each device holds until the process ends: that
+// scratch, and the twiddle factors of every line length (built by the first
+// call for the device).
+struct AsmDevice {
+  float2 *scratch = nullptr;
+  const float2 *tw = nullptr;
+};
+hipError_t asm_device(int device, AsmDevice *out);
 
-// Twiddle tables for fields of w x h: tw[0, Px) for the rows, tw[Px, Px + Py)
-// for the columns (Px, Py: the padded sizes).
-hipError_t launch_asm_twiddles(float2 *tw, uint32_t w, uint32_t h, hipStream_t st);
+// Transfer function of P for fields of w x h, tabulated over a quarter of the
+// frequency plane (asm_transfer_elems complex64: never more than h Px + Px +
+// Py).
+size_t asm_transfer_elems(uint32_t w, uint32_t h);
+hipError_t launch_asm_transfer(float2 *T, uint32_t w, uint32_t h, const AsmParams &P, hipStream_t st);
 
-// nf fields in [nf][h][w] -> out (may alias in); A, B: scratch of
-// nf * h * asm_padded(w) complex64 each; tw: the tables above.
-// hipErrorInvalidValue if a padded axis exceeds 8192 or a size is zero.
-hipError_t launch_asm(const float2 *in, float2 *out, float2 *A, float2 *B, const float2 *tw, uint32_t nf,
-                      uint32_t w, uint32_t h, const AsmParams &P, hipStream_t st);
+// nf fields in [nf][h][w] -> out (may alias in); A: scratch of
+// nf * h * asm_padded(w) complex64; H: the table above.
+hipError_t launch_asm(const float2 *in, float2 *out, float2 *A, const float2 *H, const float2 *tw, uint32_t nf,
+                      uint32_t w, uint32_t h, hipStream_t st);
 
-// Focal stacks. Row spectra of nf fields: in [nf][h][w] -> B0 [nf][Px][h]
-// (A: scratch of nf * h * Px complex64).
-hipError_t launch_asm_spectra(const float2 *in, float2 *A, float2 *B0, const float2 *tw, uint32_t nf, uint32_t w,
-                              uint32_t h, hipStream_t st);
-// The nf fields whose row spectra B0 holds, carried by the transfer function
-// of P: weight * sum over the fields of |u|^2 written into (accumulate:
-// added to) I [h][w]. B, A: scratch of nf * h * Px complex64 each; B0 is
-// kept.
-hipError_t launch_asm_intensity(const float2 *B0, float2 *B, float2 *A, const float2 *tw, uint32_t nf, uint32_t w,
-                                uint32_t h, const AsmParams &P, float *I, float weight, bool accumulate,
-                                hipStream_t st);
+// The passes by themselves. Row spectra of nrows rows [nrows][w] -> A [nrows][Px].
+hipError_t launch_asm_rows(const float2 *in, float2 *A, const float2 *tw, uint32_t nrows, uint32_t w, hipStream_t st);
+// Column passes of nf fields' row spectra src [nf][h][Px] for np planes, whose
+// tables follow each other in H -> dst [np][nf][h][Px] (src itself if np is 1).
+hipError_t launch_asm_columns(const float2 *src, float2 *dst, const float2 *H, uint32_t np, const float2 *tw,
+                              uint32_t nf, uint32_t w, uint32_t h, hipStream_t st);
+// Per plane: weight * sum over the nf fields of |u|^2, u the inverse row
+// transforms of A [np][nf][h][Px], written into (accumulate: added to) I
+// [np][h][w].
+hipError_t launch_asm_intensity(const float2 *A, const float2 *tw, uint32_t np, uint32_t nf, uint32_t w, uint32_t h,
+                                float *I, float weight, bool accumulate, hipStream_t st);
 
 }  // namespace hpt

@@ -1,156 +1,283 @@
 // Phase-only encoding on gfx950: Adam on the SLM phase under complex-amplitude
 // supervision on one plane with a phase-shift-invariant scale factor (the
 // paper's hologram encoding, Sec. 2 and Sec. 5.3). Per field and step:
-//   A = P_z exp(i phi)                          (ASM, asm.hip)
-//   s = <V, A> / <V, V>, L = ||A - s V||^2      k_enc_dots + k_enc_scale
-//   R = A - s V                                 k_enc_residual
-//   G = P_{-z} R                                (ASM: the adjoint of P_z)
-//   g = 2 Im(G conj(a)); Adam; a = exp(i phi)   k_enc_adam
-// Fields are [n][h][w] complex64; phases and Adam moments [n][h][w] float32;
-// the dot products accumulate in FP64 in a fixed order (deterministic).
+//   A = P_z exp(i phi)          k_enc_rows_phase, k_fft_columns, k_enc_ifft_dots
+//   s = <V, A> / <V, V>, L = ||A - s V||^2          the dots above, k_enc_scale
+//   G = P_{-z} (A - s V)        k_enc_rows_residual, k_fft_columns, k_enc_ifft_adam
+//   g = 2 Im(G conj(exp(i phi))); Adam                        the same kernel
+// The elementwise work runs in the first and last passes of the two
+// propagations (asm.hip), on values that are in registers there: exp(i phi)
+// is formed from phi where it is read (twice a step) instead of being kept,
+// the residual and G are never stored, and A is written once for the
+// residual. Fields are [n][h][w] complex64; phases and Adam moments
+// [n][h][w] float32; the dot products accumulate in FP64 in a fixed order
+// (deterministic).
 #include <hip/hip_runtime.h>
 
+#include "asm.hpp"
 #include "encode.hpp"
+#include "fft.hpp"
 
 namespace hpt {
 namespace {
 
+using namespace fft;
+
 constexpr int kEncBlock = 256;
 
-__global__ void __launch_bounds__(kEncBlock) k_enc_init(const float2 *U, float *phi, float2 *a, size_t n,
-                                                        uint32_t warm) {
+__global__ void __launch_bounds__(kEncBlock) k_enc_init(const float2 *U, float *phi, size_t n) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  float p;
-  if (warm) {
-    p = phi[i];
-  } else {
-    const float2 u = U[i];
-    p = (u.x == 0.f && u.y == 0.f) ? 0.f : atan2f(u.y, u.x);
-    phi[i] = p;
-  }
-  float sn, cs;
-  sincosf(p, &sn, &cs);
-  a[i] = make_float2(cs, sn);
+  const float2 u = U[i];
+  phi[i] = (u.x == 0.f && u.y == 0.f) ? 0.f : atan2f(u.y, u.x);
 }
 
-// Partial sums over block x of field f = blockIdx.y: sum conj(V) A (re, im)
-// and sum |A|^2, in FP64 -> part[(f * gridDim.x + x) * 3 + k].
-__global__ void __launch_bounds__(kEncBlock) k_enc_dots(const float2 *A, const float2 *V, double *part,
-                                                        uint32_t hw) {
-  __shared__ double sh[3][kEncBlock];
-  const uint32_t f = blockIdx.y, t = threadIdx.x;
-  const float2 *Af = A + (size_t)f * hw, *Vf = V + (size_t)f * hw;
-  double dr = 0.0, di = 0.0, aa = 0.0;
-  for (uint32_t i = blockIdx.x * kEncBlock + t; i < hw; i += gridDim.x * kEncBlock) {
-    const float2 x = Af[i], v = Vf[i];
-    dr += (double)v.x * x.x + (double)v.y * x.y;
-    di += (double)v.x * x.y - (double)v.y * x.x;
-    aa += (double)x.x * x.x + (double)x.y * x.y;
+// Row spectra of the rows [nrows][w] that `elem(i, x)` gives (i: element of
+// the array, x: column) -> A [nrows][Px]; grid (rows, fields).
+template <int LG, class F>
+__device__ __forceinline__ void rows_of(float2 *A, uint32_t w, uint32_t h, const float2 *tw, C2 *lds, F &&elem) {
+  using L = Line<LG>;
+  const uint32_t l = threadIdx.x / L::TPL, t = threadIdx.x % L::TPL;
+  const uint32_t y = blockIdx.x * Rows<LG>::kLines + l;
+  const size_t row = (size_t)blockIdx.y * h + y;
+  const bool ok = y < h;
+  C2 v[L::E];
+#pragma unroll
+  for (uint32_t q = 0; q < L::E / 2; ++q) {
+    const uint32_t i = t + q * L::TPL;
+    v[q] = ok && i < w ? elem(row * w + i) : c2(0.f, 0.f);
   }
-  sh[0][t] = dr; sh[1][t] = di; sh[2][t] = aa;
+  line_fft<LG, false, true, 1, Rows<LG>::kWave, false>(v, lds + l * L::kLds, TableTwiddles{tw}, t);
+  if (!ok) return;
+  float2 *dst = A + row * L::N;
+#pragma unroll
+  for (uint32_t q = 0; q < L::E; ++q) dst[t + q * L::TPL] = make_float2(v[q].x, v[q].y);
+}
+
+template <int LG>
+__global__ void __launch_bounds__(Rows<LG>::W) k_enc_rows_phase(const float *phi, float2 *A, uint32_t w, uint32_t h,
+                                                                const float2 *tw) {
+  __shared__ C2 lds[Rows<LG>::kLdsElems];
+  rows_of<LG>(A, w, h, tw, lds, [&](size_t i) {
+    float sn, cs;
+    sincosf(phi[i], &sn, &cs);
+    return c2(cs, sn);
+  });
+}
+
+template <int LG>
+__global__ void __launch_bounds__(Rows<LG>::W) k_enc_rows_residual(const float2 *R, const float2 *V, const double2 *s,
+                                                                   float2 *A, uint32_t w, uint32_t h,
+                                                                   const float2 *tw) {
+  __shared__ C2 lds[Rows<LG>::kLdsElems];
+  const double2 sf = s[blockIdx.y];
+  const float sr = (float)sf.x, si = (float)sf.y;
+  rows_of<LG>(A, w, h, tw, lds, [&](size_t i) {
+    const float2 v = V[i], x = R[i];
+    return c2(x.x - (sr * v.x - si * v.y), x.y - (sr * v.y + si * v.x));
+  });
+}
+
+// Inverse FFT of row y of field blockIdx.y of A [nf][h][Px], scaled: v[q], q <
+// E/2, hold elements t + q TPL (of which the first w are wanted).
+template <int LG>
+__device__ __forceinline__ void inverse_row(C2 (&v)[Line<LG>::E], const float2 *A, size_t row, bool ok, float scale,
+                                            const float2 *tw, C2 *lds) {
+  using L = Line<LG>;
+  const uint32_t l = threadIdx.x / L::TPL, t = threadIdx.x % L::TPL;
+  const float2 *src = A + row * L::N;
+#pragma unroll
+  for (uint32_t q = 0; q < L::E; ++q) {
+    const float2 g = ok ? src[t + q * L::TPL] : make_float2(0.f, 0.f);
+    v[q] = c2(g.x, g.y);
+  }
+  line_fft<LG, true, false, 1, Rows<LG>::kWave, false>(v, lds + l * L::kLds, TableTwiddles{tw}, t);
+#pragma unroll
+  for (uint32_t q = 0; q < L::E / 2; ++q) v[q] = c2(v[q].x * scale, v[q].y * scale);
+}
+
+// R = the inverse row transforms of A; partial sums of conj(V) R (re, im) and
+// |R|^2 over the workgroup's rows, in FP64 -> part[(f gridDim.x + x) 3 + k].
+// SELF: R is V, and only |R|^2 is wanted (the others are 0).
+template <int LG, bool SELF>
+__global__ void __launch_bounds__(Rows<LG>::W) k_enc_ifft_dots(const float2 *A, float2 *R, const float2 *V,
+                                                               double *part, uint32_t w, uint32_t h, float scale,
+                                                               const float2 *tw) {
+  using L = Line<LG>;
+  constexpr uint32_t W = Rows<LG>::W;
+  __shared__ C2 lds[Rows<LG>::kLdsElems];
+  __shared__ double sums[W / 64][3];
+  const uint32_t l = threadIdx.x / L::TPL, t = threadIdx.x % L::TPL;
+  const uint32_t y = blockIdx.x * Rows<LG>::kLines + l;
+  const size_t row = (size_t)blockIdx.y * h + y;
+  const bool ok = y < h;
+  C2 v[L::E];
+  inverse_row<LG>(v, A, row, ok, scale, tw, lds);
+  double dr = 0.0, di = 0.0, aa = 0.0;
+#pragma unroll
+  for (uint32_t q = 0; q < L::E / 2; ++q) {
+    const uint32_t i = t + q * L::TPL;
+    if (ok && i < w) {
+      const float2 x = make_float2(v[q].x, v[q].y);
+      R[row * w + i] = x;
+      if constexpr (!SELF) {
+        const float2 u = V[row * w + i];
+        dr += (double)u.x * x.x + (double)u.y * x.y;
+        di += (double)u.x * x.y - (double)u.y * x.x;
+      }
+      aa += (double)x.x * x.x + (double)x.y * x.y;
+    }
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    dr += __shfl_xor(dr, o); di += __shfl_xor(di, o); aa += __shfl_xor(aa, o);
+  }
+  if (threadIdx.x % 64 == 0) { double *s = sums[threadIdx.x / 64]; s[0] = dr; s[1] = di; s[2] = aa; }
   __syncthreads();
-  for (uint32_t s = kEncBlock / 2; s > 0; s >>= 1) {
-    if (t < s)
-      for (int k = 0; k < 3; ++k) sh[k][t] += sh[k][t + s];
+  if (threadIdx.x < 3) {
+    double a = 0.0;
+    for (uint32_t k = 0; k < W / 64; ++k) a += sums[k][threadIdx.x];
+    part[((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 3 + threadIdx.x] = a;
+  }
+}
+
+// Field blockIdx.x: sum of its nb partials. NORM: vv[f] = <V, V>; else the
+// optimal scale s = <V, A> / <V, V> and the relative loss 1 - |<V, A>|^2 /
+// (<V, V> <A, A>).
+template <bool NORM>
+__global__ void __launch_bounds__(kEncBlock) k_enc_scale(const double *part, uint32_t nb, double *vv, double2 *s,
+                                                         double *rel) {
+  __shared__ double sh[3][kEncBlock];
+  const uint32_t f = blockIdx.x, t = threadIdx.x;
+  double a[3] = {0.0, 0.0, 0.0};
+  for (uint32_t b = t; b < nb; b += kEncBlock)
+    for (int k = 0; k < 3; ++k) a[k] += part[((size_t)f * nb + b) * 3 + k];
+  for (int k = 0; k < 3; ++k) sh[k][t] = a[k];
+  __syncthreads();
+  for (uint32_t o = kEncBlock / 2; o > 0; o >>= 1) {
+    if (t < o)
+      for (int k = 0; k < 3; ++k) sh[k][t] += sh[k][t + o];
     __syncthreads();
   }
-  if (t < 3) part[((size_t)f * gridDim.x + blockIdx.x) * 3 + t] = sh[t][0];
-}
-
-// Per field: the optimal scale s = <V, A> / <V, V> and the relative loss
-// 1 - |<V, A>|^2 / (<V, V> <A, A>); vv[f] = <V, V>.
-__global__ void k_enc_scale(const double *part, uint32_t nb, uint32_t n, const double *vv, double2 *s,
-                            double *rel) {
-  const uint32_t f = blockIdx.x * blockDim.x + threadIdx.x;
-  if (f >= n) return;
-  double dr = 0.0, di = 0.0, aa = 0.0;
-  for (uint32_t b = 0; b < nb; ++b) {
-    const double *p = part + ((size_t)f * nb + b) * 3;
-    dr += p[0]; di += p[1]; aa += p[2];
-  }
+  if (t != 0) return;
+  const double dr = sh[0][0], di = sh[1][0], aa = sh[2][0];
+  if (NORM) { vv[f] = aa; return; }
   const double v = vv[f];
   s[f] = v > 0.0 ? make_double2(dr / v, di / v) : make_double2(0.0, 0.0);
   rel[f] = (v > 0.0 && aa > 0.0) ? 1.0 - (dr * dr + di * di) / (v * aa) : 1.0;
 }
 
-// <V, V> per field from the third partial of k_enc_dots(V, V).
-__global__ void k_enc_norm(const double *part, uint32_t nb, uint32_t n, double *vv) {
-  const uint32_t f = blockIdx.x * blockDim.x + threadIdx.x;
-  if (f >= n) return;
-  double aa = 0.0;
-  for (uint32_t b = 0; b < nb; ++b) aa += part[((size_t)f * nb + b) * 3 + 2];
-  vv[f] = aa;
+// G = the inverse row transforms of A; g = 2 Im(G conj(exp(i phi))); Adam.
+// FIRST: the moments are zero before this step and are not read.
+template <int LG, bool FIRST>
+__global__ void __launch_bounds__(Rows<LG>::W) k_enc_ifft_adam(const float2 *A, float *phi, float *m, float *v2,
+                                                               uint32_t w, uint32_t h, float scale, float lr,
+                                                               float bc1, float bc2, const float2 *tw) {
+  using L = Line<LG>;
+  __shared__ C2 lds[Rows<LG>::kLdsElems];
+  const uint32_t l = threadIdx.x / L::TPL, t = threadIdx.x % L::TPL;
+  const uint32_t y = blockIdx.x * Rows<LG>::kLines + l;
+  const size_t row = (size_t)blockIdx.y * h + y;
+  const bool ok = y < h;
+  C2 v[L::E];
+  inverse_row<LG>(v, A, row, ok, scale, tw, lds);
+#pragma unroll
+  for (uint32_t q = 0; q < L::E / 2; ++q) {
+    const uint32_t x = t + q * L::TPL;
+    if (!ok || x >= w) continue;
+    const size_t i = row * w + x;
+    const float p0 = phi[i];
+    float sn, cs;
+    sincosf(p0, &sn, &cs);
+    const float g = 2.0f * (v[q].y * cs - v[q].x * sn);
+    const float m0 = FIRST ? 0.f : m[i], v0 = FIRST ? 0.f : v2[i];
+    const float mi = kAdamBeta1 * m0 + (1.0f - kAdamBeta1) * g;
+    const float vi = kAdamBeta2 * v0 + (1.0f - kAdamBeta2) * g * g;
+    m[i] = mi;
+    v2[i] = vi;
+    phi[i] = p0 - lr * (mi / bc1) / (sqrtf(vi / bc2) + kAdamEps);
+  }
 }
 
-__global__ void __launch_bounds__(kEncBlock) k_enc_residual(float2 *A, const float2 *V, const double2 *s,
-                                                            uint32_t hw, size_t n) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const double2 sf = s[i / hw];
-  const float sr = (float)sf.x, si = (float)sf.y;
-  const float2 v = V[i], x = A[i];
-  A[i] = make_float2(x.x - (sr * v.x - si * v.y), x.y - (sr * v.y + si * v.x));
+template <int LG>
+dim3 row_grid(uint32_t nf, uint32_t h) { return dim3((h + Rows<LG>::kLines - 1) / Rows<LG>::kLines, nf); }
+
+// Rows of w values: f(integral_constant<LG>) for their padded length.
+template <class F>
+hipError_t for_rows(uint32_t w, F &&f) {
+  return with_length(log2u(asm_padded(w)), f) ? hipGetLastError() : hipErrorInvalidValue;
 }
 
-__global__ void __launch_bounds__(kEncBlock) k_enc_adam(float *phi, float *m, float *v, float2 *a,
-                                                        const float2 *G, size_t n, float lr, float bc1,
-                                                        float bc2) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float2 g2 = G[i], ai = a[i];
-  const float g = 2.0f * (g2.y * ai.x - g2.x * ai.y);  // 2 Im(G conj(a))
-  const float mi = kAdamBeta1 * m[i] + (1.0f - kAdamBeta1) * g;
-  const float vi = kAdamBeta2 * v[i] + (1.0f - kAdamBeta2) * g * g;
-  m[i] = mi;
-  v[i] = vi;
-  const float p = phi[i] - lr * (mi / bc1) / (sqrtf(vi / bc2) + kAdamEps);
-  phi[i] = p;
-  float sn, cs;
-  sincosf(p, &sn, &cs);
-  a[i] = make_float2(cs, sn);
-}
-
-inline uint32_t grid1(size_t n) { return (uint32_t)((n + kEncBlock - 1) / kEncBlock); }
+float fft_scale(uint32_t w, uint32_t h) { return 1.0f / ((float)asm_padded(w) * (float)asm_padded(h)); }
 
 }  // namespace
 
-uint32_t enc_dot_blocks(uint32_t hw) {
-  const uint32_t b = (hw + kEncBlock * 8 - 1) / (kEncBlock * 8);
-  return b < 1 ? 1 : (b > 256 ? 256 : b);
+uint32_t enc_parts(uint32_t w, uint32_t h) {
+  uint32_t n = h;
+  with_length(log2u(asm_padded(w)), [&](auto lg) { n = row_grid<decltype(lg)::value>(1, h).x; });
+  return n;
 }
 
-hipError_t launch_enc_init(const float2 *U, float *phi, float2 *a, size_t n, bool warm, hipStream_t st) {
-  hipLaunchKernelGGL(k_enc_init, dim3(grid1(n)), dim3(kEncBlock), 0, st, U, phi, a, n, warm ? 1u : 0u);
+hipError_t launch_enc_init(const float2 *U, float *phi, size_t n, hipStream_t st) {
+  hipLaunchKernelGGL(k_enc_init, dim3((uint32_t)((n + kEncBlock - 1) / kEncBlock)), dim3(kEncBlock), 0, st, U, phi, n);
   return hipGetLastError();
 }
 
-hipError_t launch_enc_norm(const float2 *V, double *part, double *vv, uint32_t nf, uint32_t hw, hipStream_t st) {
-  const uint32_t nb = enc_dot_blocks(hw);
-  hipLaunchKernelGGL(k_enc_dots, dim3(nb, nf), dim3(kEncBlock), 0, st, V, V, part, hw);
-  hipLaunchKernelGGL(k_enc_norm, dim3((nf + 63) / 64), dim3(64), 0, st, part, nb, nf, vv);
+hipError_t launch_enc_target(const float2 *A, float2 *V, double *part, double *vv, const float2 *tw, uint32_t nf,
+                             uint32_t w, uint32_t h, hipStream_t st) {
+  const float2 *t = tw + 2 * asm_padded(w);
+  hipError_t e = for_rows(w, [&](auto lg) {
+    constexpr int LG = decltype(lg)::value;
+    hipLaunchKernelGGL((k_enc_ifft_dots<LG, true>), row_grid<LG>(nf, h), dim3(Rows<LG>::W), 0, st, A, V, nullptr, part,
+                       w, h, fft_scale(w, h), t);
+  });
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_enc_scale<true>, dim3(nf), dim3(kEncBlock), 0, st, part, enc_parts(w, h), vv, nullptr, nullptr);
   return hipGetLastError();
 }
 
-hipError_t launch_enc_scale(const float2 *A, const float2 *V, double *part, const double *vv, double2 *s,
-                            double *rel, uint32_t nf, uint32_t hw, hipStream_t st) {
-  const uint32_t nb = enc_dot_blocks(hw);
-  hipLaunchKernelGGL(k_enc_dots, dim3(nb, nf), dim3(kEncBlock), 0, st, A, V, part, hw);
-  hipLaunchKernelGGL(k_enc_scale, dim3((nf + 63) / 64), dim3(64), 0, st, part, nb, nf, vv, s, rel);
+hipError_t launch_enc_rows_phase(const float *phi, float2 *A, const float2 *tw, uint32_t nf, uint32_t w, uint32_t h,
+                                 hipStream_t st) {
+  return for_rows(w, [&](auto lg) {
+    constexpr int LG = decltype(lg)::value;
+    hipLaunchKernelGGL((k_enc_rows_phase<LG>), row_grid<LG>(nf, h), dim3(Rows<LG>::W), 0, st, phi, A, w, h,
+                       tw + 2 * asm_padded(w));
+  });
+}
+
+hipError_t launch_enc_scale(const float2 *A, float2 *R, const float2 *V, double *part, double *vv, double2 *s,
+                            double *rel, const float2 *tw, uint32_t nf, uint32_t w, uint32_t h, hipStream_t st) {
+  const float2 *t = tw + 2 * asm_padded(w);
+  hipError_t e = for_rows(w, [&](auto lg) {
+    constexpr int LG = decltype(lg)::value;
+    hipLaunchKernelGGL((k_enc_ifft_dots<LG, false>), row_grid<LG>(nf, h), dim3(Rows<LG>::W), 0, st, A, R, V, part, w, h,
+                       fft_scale(w, h), t);
+  });
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_enc_scale<false>, dim3(nf), dim3(kEncBlock), 0, st, part, enc_parts(w, h), vv, s, rel);
   return hipGetLastError();
 }
 
-hipError_t launch_enc_residual(float2 *A, const float2 *V, const double2 *s, uint32_t nf, uint32_t hw,
-                               hipStream_t st) {
-  const size_t n = (size_t)nf * hw;
-  hipLaunchKernelGGL(k_enc_residual, dim3(grid1(n)), dim3(kEncBlock), 0, st, A, V, s, hw, n);
-  return hipGetLastError();
+hipError_t launch_enc_rows_residual(const float2 *R, const float2 *V, const double2 *s, float2 *A, const float2 *tw,
+                                    uint32_t nf, uint32_t w, uint32_t h, hipStream_t st) {
+  return for_rows(w, [&](auto lg) {
+    constexpr int LG = decltype(lg)::value;
+    hipLaunchKernelGGL((k_enc_rows_residual<LG>), row_grid<LG>(nf, h), dim3(Rows<LG>::W), 0, st, R, V, s, A, w, h,
+                       tw + 2 * asm_padded(w));
+  });
 }
 
-hipError_t launch_enc_adam(float *phi, float *m, float *v, float2 *a, const float2 *G, size_t n, float lr,
-                           float bc1, float bc2, hipStream_t st) {
-  hipLaunchKernelGGL(k_enc_adam, dim3(grid1(n)), dim3(kEncBlock), 0, st, phi, m, v, a, G, n, lr, bc1, bc2);
-  return hipGetLastError();
+hipError_t launch_enc_adam(const float2 *A, float *phi, float *m, float *v, const float2 *tw, uint32_t nf, uint32_t w,
+                           uint32_t h, float lr, float bc1, float bc2, bool first, hipStream_t st) {
+  const float2 *t = tw + 2 * asm_padded(w);
+  return for_rows(w, [&](auto lg) {
+    constexpr int LG = decltype(lg)::value;
+    if (first)
+      hipLaunchKernelGGL((k_enc_ifft_adam<LG, true>), row_grid<LG>(nf, h), dim3(Rows<LG>::W), 0, st, A, phi, m, v, w, h,
+                         fft_scale(w, h), lr, bc1, bc2, t);
+    else
+      hipLaunchKernelGGL((k_enc_ifft_adam<LG, false>), row_grid<LG>(nf, h), dim3(Rows<LG>::W), 0, st, A, phi, m, v, w, h,
+                         fft_scale(w, h), lr, bc1, bc2, t);
+  });
 }
 
 }  // namespace hpt

@@ -197,11 +197,23 @@ struct hpt_ctx {
   } slots[2];
   uint64_t batches = 0, jobs_done = 0;
   uint32_t fail_batches = 0;  // failure injection (hpt_debug_fail_batches)
-  float2 *na_scratch = nullptr;  // this device's static scratch of the allocation-free propagation
+  AsmDevice fft;              // this device's twiddle table and static scratch of the propagation
   // profiling (guarded by mu; events used by the scheduler thread only)
   uint32_t profile = 0;
   hpt_kernel_time ktime[HPT_K_KINDS] = {};
   uint64_t node_visits = 0, prim_tests = 0;
+
+  // Work buffers of a propagation, reconstruction or encoding: one allocation.
+  struct Scratch {
+    char *p = nullptr;
+    size_t bytes = 0, at = 0;
+    template <class T>
+    T *take(size_t n) {  // the next n values, on a 256-byte boundary
+      T *r = (T *)(p + at);
+      at += (n * sizeof(T) + 255) / 256 * 256;
+      return r;
+    }
+  };
 
   hipError_t alloc(void **p, size_t bytes) {
     hipError_t e = hipMalloc(p, bytes ? bytes : 16);
@@ -830,10 +842,10 @@ hpt_status hpt_create(int device, uint64_t budget, hpt_ctx **out) {
   if (hipSetDevice(device) != hipSuccess) return fail(HPT_ENODEV, "hipSetDevice failed");
   auto C = std::make_unique<hpt_ctx>();
   C->device = device;
-  // device address of the allocation-free propagation's static scratch,
-  // taken once per device with the device current
-  if (hipError_t e = asm_noalloc_scratch(device, &C->na_scratch); e != hipSuccess)
-    return fail(HPT_EDEVICE, std::string("scratch symbol lookup failed: ") + hipGetErrorString(e));
+  // device addresses of the propagation's static scratch and twiddle table
+  // (built by the device's first context), with the device current
+  if (hipError_t e = asm_device(device, &C->fft); e != hipSuccess)
+    return fail(HPT_EDEVICE, std::string("propagation tables: ") + hipGetErrorString(e));
   size_t free_b = 0, total_b = 0;
   (void)hipMemGetInfo(&free_b, &total_b);
   C->budget = budget ? budget : (uint64_t)(0.9 * (double)free_b);
@@ -1479,8 +1491,30 @@ hpt_status hpt_grf_read(hpt_ctx *C, uint32_t gw, uint32_t gh, uint32_t T, uint64
 // Fields per launch of the FFT passes: their grids index fields in a
 // dimension limited to 65535 blocks.
 constexpr uint32_t kMaxFieldsPerLaunch = 65535;
+constexpr uint32_t kEncBuffers = 11;  // buffers the encoding takes of its scratch (256-byte boundaries)
+// Work buffers of a call: fields are taken in chunks of at most this much.
+// Propagation: four 1080p fields, whose row spectra the memory-side cache
+// holds between the passes (24 of them: 1.90 ms; in chunks of 256 MiB 2.00,
+// of 1 GiB 1.95). Encoding: 512 MiB, where a launch still has six fields to
+// spread over the CUs (150 MiB, one field: 121 ms instead of 94). Focal
+// stacks: planes times frames.
+constexpr uint64_t kAsmChunkBytes = 160ull << 20, kEncChunkBytes = 512ull << 20, kStackChunkBytes = 1ull << 30;
 
 namespace {
+// Work buffers (lock held). scratch_room: bytes a call may take, after making
+// room for `least`.
+uint64_t scratch_room(hpt_ctx *C, uint64_t least) {
+  auto room = [&] { return C->budget > C->used ? C->budget - C->used : 0; };
+  if (room() < least) evict_grfs(C, least);
+  return room();
+}
+bool scratch_take(hpt_ctx *C, size_t bytes, hpt_ctx::Scratch &S) {
+  if (C->alloc((void **)&S.p, bytes) != hipSuccess) return false;
+  S.bytes = bytes;
+  return true;
+}
+void scratch_give(hpt_ctx *C, hpt_ctx::Scratch &S) { C->release(S.p, S.bytes); }
+
 // Order the work about to be enqueued on `work` after everything enqueued on
 // the caller's stream so far (no-op for a null caller stream).
 hipError_t after_caller(hipStream_t work, void *caller) {
@@ -1527,48 +1561,34 @@ hpt_status hpt_asm_propagate(hpt_ctx *C, const void *d_in, void *d_out, uint32_t
   if (flags & ~HPT_ASM_BAND_LIMIT) return fail(HPT_EINVAL, "unknown flags");
   const uint32_t px = asm_padded(width), py = asm_padded(height);
   const AsmParams P = asm_params(width, height, pitch, lambda, distance, flags, 0.0);
-  // scratch for a chunk of fields: two [h][Px] complex64 buffers per field
-  const uint64_t per = 2ull * height * px * sizeof(float2);
-  float2 *A = nullptr, *B = nullptr, *W = nullptr;
-  const size_t tw_bytes = (size_t)(px + py) * sizeof(float2);  // twiddle tables
+  // scratch: one [h][Px] complex64 buffer per field of a chunk, and the transfer function
+  const uint64_t per = (uint64_t)height * px * sizeof(float2);
+  const size_t h_elems = asm_transfer_elems(width, height), h_bytes = h_elems * sizeof(float2) + 256;
+  hpt_ctx::Scratch S;
   uint32_t chunk = 0;
   {
     std::lock_guard<std::mutex> g(C->mu);
     (void)hipSetDevice(C->device);
-    uint64_t free_b = C->budget > C->used ? C->budget - C->used : 0;
-    if (free_b < per) evict_grfs(C, per);
-    free_b = C->budget > C->used ? C->budget - C->used : 0;
-    chunk = (uint32_t)std::min<uint64_t>({(uint64_t)n_fields, free_b / per, std::max<uint64_t>(1, (1ull << 30) / per),
-                                           (uint64_t)kMaxFieldsPerLaunch});
+    const uint64_t room = scratch_room(C, per + h_bytes);
+    chunk = (uint32_t)std::min<uint64_t>({(uint64_t)n_fields, room > h_bytes ? (room - h_bytes) / per : 0,
+                                           std::max<uint64_t>(1, kAsmChunkBytes / per), (uint64_t)kMaxFieldsPerLaunch});
     if (chunk == 0) return fail(HPT_EBUDGET, "propagation scratch does not fit the budget");
-    const size_t half = (size_t)chunk * height * px * sizeof(float2);
-    if (C->alloc((void **)&A, half) != hipSuccess) return fail(HPT_ENOMEM, "scratch allocation failed");
-    if (C->alloc((void **)&B, half) != hipSuccess) {
-      C->release(A, half);
-      return fail(HPT_ENOMEM, "scratch allocation failed");
-    }
-    if (C->alloc((void **)&W, tw_bytes) != hipSuccess) {
-      C->release(A, half);
-      C->release(B, half);
-      return fail(HPT_ENOMEM, "scratch allocation failed");
-    }
+    if (!scratch_take(C, chunk * per + h_bytes, S)) return fail(HPT_ENOMEM, "scratch allocation failed");
   }
+  float2 *H = S.take<float2>(h_elems), *A = S.take<float2>((size_t)chunk * height * px);
   hipError_t e = after_caller(C->aux, hip_stream);
-  if (e == hipSuccess) e = launch_asm_twiddles(W, width, height, C->aux);
+  if (e == hipSuccess) e = launch_asm_transfer(H, width, height, P, C->aux);
   const size_t field = (size_t)width * height;
   for (uint32_t f0 = 0; f0 < n_fields && e == hipSuccess; f0 += chunk) {
     uint32_t nf = std::min(chunk, n_fields - f0);
-    e = launch_asm((const float2 *)d_in + f0 * field, (float2 *)d_out + f0 * field, A, B, W, nf, width, height,
-                   P, C->aux);
+    e = launch_asm((const float2 *)d_in + f0 * field, (float2 *)d_out + f0 * field, A, H, C->fft.tw, nf, width, height,
+                   C->aux);
   }
   if (e == hipSuccess) e = hipStreamSynchronize(C->aux);
   else (void)hipStreamSynchronize(C->aux);  // launches already queued still use the scratch
   {
     std::lock_guard<std::mutex> g(C->mu);
-    const size_t half = (size_t)chunk * height * px * sizeof(float2);
-    C->release(A, half);
-    C->release(B, half);
-    C->release(W, tw_bytes);
+    scratch_give(C, S);
   }
   if (e != hipSuccess) return fail(HPT_EDEVICE, std::string("propagation failed: ") + hipGetErrorString(e));
   return HPT_OK;
@@ -1592,15 +1612,16 @@ hpt_status hpt_asm_propagate_noalloc(hpt_ctx *C, const void *d_in, void *d_out, 
   const uint32_t chunk = (uint32_t)std::min<size_t>({(size_t)n_fields, (kNoAllocScratchElems - tw) / (2 * per),
                                                      (size_t)kMaxFieldsPerLaunch});
   const AsmParams P = asm_params(width, height, pitch, lambda, distance, flags, 0.0);
-  // scratch: twiddle tables, then the two work buffers of a chunk of fields
-  float2 *W = C->na_scratch, *A = W + tw, *B = A + (size_t)chunk * height * px;
+  // scratch: the transfer function (at most per + tw elements), then the
+  // work buffers of a chunk of fields
+  float2 *H = C->fft.scratch, *A = H + up(asm_transfer_elems(width, height));
   hipStream_t st = hip_stream ? (hipStream_t)hip_stream : C->aux;
   (void)hipSetDevice(C->device);
-  hipError_t e = launch_asm_twiddles(W, width, height, st);
+  hipError_t e = launch_asm_transfer(H, width, height, P, st);
   const size_t field = (size_t)width * height;
   for (uint32_t f0 = 0; f0 < n_fields && e == hipSuccess; f0 += chunk) {
     const uint32_t nf = std::min(chunk, n_fields - f0);
-    e = launch_asm((const float2 *)d_in + f0 * field, (float2 *)d_out + f0 * field, A, B, W, nf, width, height, P,
+    e = launch_asm((const float2 *)d_in + f0 * field, (float2 *)d_out + f0 * field, A, H, C->fft.tw, nf, width, height,
                    st);
   }
   if (e == hipSuccess && !hip_stream) e = hipStreamSynchronize(st);
@@ -1623,66 +1644,68 @@ hpt_status hpt_encode_phase(hpt_ctx *C, const void *d_fields, uint32_t n_fields,
   const AsmParams Pf = asm_params(width, height, pitch, lambda, distance, bl, 0.0);
   const AsmParams Pb = asm_params(width, height, pitch, lambda, -distance, bl, 0.0);
   const uint32_t hw = width * height;
-  const uint32_t nb = enc_dot_blocks(hw);
-  // per field: target V, phasor a, work field R (complex64), Adam moments m, v
-  // (float), two ASM buffers [h][Px], dot partials, |V|^2, scale
-  const uint64_t per = 32ull * hw + 16ull * height * px + 24ull * nb + 8 + 16;
-  const size_t tw_bytes = (size_t)(px + py) * sizeof(float2);
+  const uint32_t nb = enc_parts(width, height);
+  // per field: target V, work field R (complex64), Adam moments m, v (float),
+  // the ASM's buffer [h][Px], dot partials, |V|^2, scale; per call the
+  // transfer functions of the two directions (one buffer, tabulated again for
+  // every direction, where the budget has no room for both)
+  const uint64_t per = 24ull * hw + 8ull * height * px + 24ull * nb + 8 + 16;
+  const size_t h_elems = asm_transfer_elems(width, height), h_bytes = h_elems * sizeof(float2);
   const size_t rel_bytes = (size_t)n_fields * sizeof(double);
-  std::vector<std::pair<void **, size_t>> bufs;
-  float2 *V = nullptr, *a = nullptr, *R = nullptr, *A = nullptr, *B = nullptr, *W = nullptr;
-  float *m = nullptr, *v = nullptr;
-  double *part = nullptr, *vv = nullptr, *rel = nullptr;
-  double2 *sc = nullptr;
+  hpt_ctx::Scratch S;
   uint32_t chunk = 0;
+  bool two = false;
   {
     std::lock_guard<std::mutex> g(C->mu);
     (void)hipSetDevice(C->device);
-    const uint64_t fixed = tw_bytes + rel_bytes;
-    uint64_t free_b = C->budget > C->used ? C->budget - C->used : 0;
-    if (free_b < per + fixed) evict_grfs(C, per + fixed);
-    free_b = C->budget > C->used ? C->budget - C->used : 0;
-    free_b = free_b > fixed ? free_b - fixed : 0;
-    chunk = (uint32_t)std::min<uint64_t>({(uint64_t)n_fields, free_b / per, std::max<uint64_t>(1, (1ull << 30) / per),
-                                           (uint64_t)kMaxFieldsPerLaunch});
+    uint64_t fixed = h_bytes + rel_bytes + kEncBuffers * 256;
+    uint64_t room = scratch_room(C, per + fixed);
+    two = room >= per + fixed + h_bytes;
+    if (two) fixed += h_bytes;
+    chunk = (uint32_t)std::min<uint64_t>({(uint64_t)n_fields, room > fixed ? (room - fixed) / per : 0,
+                                           std::max<uint64_t>(1, kEncChunkBytes / per), (uint64_t)kMaxFieldsPerLaunch});
     if (chunk == 0) return fail(HPT_EBUDGET, "encoding scratch does not fit the budget");
-    const size_t f = (size_t)chunk * hw, ap = (size_t)chunk * height * px;
-    bufs = {{(void **)&V, 8 * f}, {(void **)&a, 8 * f}, {(void **)&R, 8 * f}, {(void **)&m, 4 * f},
-            {(void **)&v, 4 * f}, {(void **)&A, 8 * ap}, {(void **)&B, 8 * ap},
-            {(void **)&part, (size_t)chunk * nb * 3 * sizeof(double)}, {(void **)&vv, chunk * sizeof(double)},
-            {(void **)&sc, chunk * sizeof(double2)}, {(void **)&rel, rel_bytes}, {(void **)&W, tw_bytes}};
-    bool ok = true;
-    for (auto &b : bufs) ok = ok && C->alloc(b.first, b.second) == hipSuccess;
-    if (!ok) {
-      for (auto &b : bufs)
-        if (*b.first) C->release(*b.first, b.second);
-      return fail(HPT_ENOMEM, "scratch allocation failed");
-    }
+    if (!scratch_take(C, chunk * per + fixed, S)) return fail(HPT_ENOMEM, "scratch allocation failed");
   }
+  const size_t fn = (size_t)chunk * hw;
+  float2 *V = S.take<float2>(fn), *R = S.take<float2>(fn), *A = S.take<float2>((size_t)chunk * height * px);
+  float *m = S.take<float>(fn), *v = S.take<float>(fn);
+  double *part = S.take<double>((size_t)chunk * nb * 3), *vv = S.take<double>(chunk);
+  double2 *sc = S.take<double2>(chunk);
+  double *rel = S.take<double>(n_fields);
+  float2 *Hf = S.take<float2>(h_elems), *Hb = two ? S.take<float2>(h_elems) : nullptr;
   hipStream_t st = C->aux;
   hipError_t e = after_caller(st, hip_stream);
-  if (e == hipSuccess) e = launch_asm_twiddles(W, width, height, st);
+  if (two) {
+    if (e == hipSuccess) e = launch_asm_transfer(Hf, width, height, Pf, st);
+    if (e == hipSuccess) e = launch_asm_transfer(Hb, width, height, Pb, st);
+  }
+  const float2 *tw = C->fft.tw;
+  // the column passes of one direction, on A
+  auto columns = [&](bool back, uint32_t nf) {
+    hipError_t r = two ? hipSuccess : launch_asm_transfer(Hf, width, height, back ? Pb : Pf, st);
+    return r == hipSuccess ? launch_asm_columns(A, A, two && back ? Hb : Hf, 1, tw, nf, width, height, st) : r;
+  };
   const bool warm = (flags & HPT_ENCODE_WARM_START) != 0;
   for (uint32_t f0 = 0; f0 < n_fields && e == hipSuccess; f0 += chunk) {
     const uint32_t nf = std::min(chunk, n_fields - f0);
-    const size_t n = (size_t)nf * hw;
     const float2 *U = (const float2 *)d_fields + (size_t)f0 * hw;
     float *phi = (float *)d_phase + (size_t)f0 * hw;
-    e = launch_asm(U, V, A, B, W, nf, width, height, Pf, st);
-    if (e == hipSuccess) e = launch_enc_norm(V, part, vv, nf, hw, st);
-    if (e == hipSuccess) e = launch_enc_init(U, phi, a, n, warm, st);
-    if (e == hipSuccess) e = hipMemsetAsync(m, 0, 4 * n, st);
-    if (e == hipSuccess) e = hipMemsetAsync(v, 0, 4 * n, st);
-    for (uint32_t k = 1; k <= iterations && e == hipSuccess; ++k) {
-      e = launch_asm(a, R, A, B, W, nf, width, height, Pf, st);
-      if (e == hipSuccess) e = launch_enc_scale(R, V, part, vv, sc, rel + f0, nf, hw, st);
-      if (e == hipSuccess) e = launch_enc_residual(R, V, sc, nf, hw, st);
-      if (e == hipSuccess) e = launch_asm(R, R, A, B, W, nf, width, height, Pb, st);
+    e = launch_asm_rows(U, A, tw, nf * height, width, st);
+    if (e == hipSuccess) e = columns(false, nf);
+    if (e == hipSuccess) e = launch_enc_target(A, V, part, vv, tw, nf, width, height, st);
+    if (e == hipSuccess && !warm) e = launch_enc_init(U, phi, (size_t)nf * hw, st);
+    for (uint32_t k = 1; k <= iterations + 1 && e == hipSuccess; ++k) {
+      e = launch_enc_rows_phase(phi, A, tw, nf, width, height, st);
+      if (e == hipSuccess) e = columns(false, nf);
+      if (e == hipSuccess) e = launch_enc_scale(A, R, V, part, vv, sc, rel + f0, tw, nf, width, height, st);
+      if (k > iterations) break;  // the final loss
+      if (e == hipSuccess) e = launch_enc_rows_residual(R, V, sc, A, tw, nf, width, height, st);
+      if (e == hipSuccess) e = columns(true, nf);
       const float bc1 = (float)(1.0 - std::pow(0.9, (double)k)), bc2 = (float)(1.0 - std::pow(0.999, (double)k));
-      if (e == hipSuccess) e = launch_enc_adam(phi, m, v, a, R, n, (float)lr, bc1, bc2, st);
+      if (e == hipSuccess)
+        e = launch_enc_adam(A, phi, m, v, tw, nf, width, height, (float)lr, bc1, bc2, k == 1, st);
     }
-    if (e == hipSuccess) e = launch_asm(a, R, A, B, W, nf, width, height, Pf, st);
-    if (e == hipSuccess) e = launch_enc_scale(R, V, part, vv, sc, rel + f0, nf, hw, st);
   }
   std::vector<double> rel_h(n_fields, 0.0);
   if (e == hipSuccess) e = hipMemcpyAsync(rel_h.data(), rel, rel_bytes, hipMemcpyDeviceToHost, st);
@@ -1690,7 +1713,7 @@ hpt_status hpt_encode_phase(hpt_ctx *C, const void *d_fields, uint32_t n_fields,
   else (void)hipStreamSynchronize(st);  // launches already queued still use the scratch
   {
     std::lock_guard<std::mutex> g(C->mu);
-    for (auto &b : bufs) C->release(*b.first, b.second);
+    scratch_give(C, S);
   }
   if (e != hipSuccess) return fail(HPT_EDEVICE, std::string("encoding failed: ") + hipGetErrorString(e));
   if (loss_out) std::copy(rel_h.begin(), rel_h.end(), loss_out);
@@ -1712,48 +1735,44 @@ hpt_status hpt_reconstruct(hpt_ctx *C, const void *d_fields, uint32_t n_ch, uint
     if (!std::isfinite(distances[p])) return fail(HPT_EINVAL, "bad distance");
   if (flags & ~HPT_ASM_BAND_LIMIT) return fail(HPT_EINVAL, "unknown flags");
   const uint32_t px = asm_padded(width), py = asm_padded(height);
-  // scratch per frame of a chunk: row spectra (kept over the planes) and two work buffers
-  const uint64_t per = 3ull * height * px * sizeof(float2);
-  const size_t tw_bytes = (size_t)(px + py) * sizeof(float2);
-  float2 *A = nullptr, *B = nullptr, *B0 = nullptr, *W = nullptr;
-  uint32_t chunk = 0;
-  size_t third = 0;
+  // scratch: per frame of a chunk its row spectra (kept over the planes) and
+  // a work buffer for each of the planes taken at a time, whose transfer
+  // functions are kept for the call's channel
+  const uint64_t one = (uint64_t)height * px * sizeof(float2);
+  const size_t h_elems = asm_transfer_elems(width, height), h_bytes = h_elems * sizeof(float2);
+  hpt_ctx::Scratch W;
+  uint32_t chunk = 0, group = 0;   // frames, planes at a time
   {
     std::lock_guard<std::mutex> g(C->mu);
     (void)hipSetDevice(C->device);
-    uint64_t free_b = C->budget > C->used ? C->budget - C->used : 0;
-    if (free_b < per + tw_bytes) evict_grfs(C, per + tw_bytes);
-    free_b = C->budget > C->used ? C->budget - C->used : 0;
-    free_b = free_b > tw_bytes ? free_b - tw_bytes : 0;
-    chunk = (uint32_t)std::min<uint64_t>({(uint64_t)T, free_b / per, std::max<uint64_t>(1, (1ull << 30) / per),
+    const uint64_t least = 2 * one + h_bytes + 3 * 256, free_b = scratch_room(C, least);
+    if (free_b < least) return fail(HPT_EBUDGET, "reconstruction scratch does not fit the budget");
+    const uint64_t room = std::min<uint64_t>(free_b, std::max<uint64_t>(kStackChunkBytes, least)) - 3 * 256;
+    group = (uint32_t)std::min<uint64_t>(n_planes, (room - one) / (one + h_bytes));
+    chunk = (uint32_t)std::min<uint64_t>({(uint64_t)T, (room - group * h_bytes) / ((group + 1) * one),
                                            (uint64_t)kMaxFieldsPerLaunch});
-    if (chunk == 0) return fail(HPT_EBUDGET, "reconstruction scratch does not fit the budget");
-    third = (size_t)chunk * height * px * sizeof(float2);
-    bool ok = C->alloc((void **)&A, third) == hipSuccess;
-    ok = ok && C->alloc((void **)&B, third) == hipSuccess;
-    ok = ok && C->alloc((void **)&B0, third) == hipSuccess;
-    ok = ok && C->alloc((void **)&W, tw_bytes) == hipSuccess;
-    if (!ok) {
-      if (A) C->release(A, third);
-      if (B) C->release(B, third);
-      if (B0) C->release(B0, third);
-      if (W) C->release(W, tw_bytes);
+    if (!scratch_take(C, (group + 1) * chunk * one + group * h_bytes + 3 * 256, W))
       return fail(HPT_ENOMEM, "scratch allocation failed");
-    }
   }
+  float2 *S = W.take<float2>((size_t)chunk * height * px), *A = W.take<float2>((size_t)group * chunk * height * px);
+  float2 *H = W.take<float2>(group * h_elems);
   hipError_t e = after_caller(C->aux, hip_stream);
-  if (e == hipSuccess) e = launch_asm_twiddles(W, width, height, C->aux);
   const size_t field = (size_t)width * height;
   const float weight = 1.0f / (float)T;
+  const float2 *tw = C->fft.tw;
   for (uint32_t c = 0; c < n_ch && e == hipSuccess; ++c) {
     for (uint32_t t0 = 0; t0 < T && e == hipSuccess; t0 += chunk) {
       const uint32_t nf = std::min(chunk, T - t0);
-      e = launch_asm_spectra((const float2 *)d_fields + ((size_t)c * T + t0) * field, A, B0, W, nf, width, height,
-                             C->aux);
-      for (uint32_t p = 0; p < n_planes && e == hipSuccess; ++p) {
-        const AsmParams P = asm_params(width, height, pitch, lambdas[c], distances[p], flags, na);
-        float *I = (float *)d_out + ((size_t)c * n_planes + p) * field;
-        e = launch_asm_intensity(B0, B, A, W, nf, width, height, P, I, weight, t0 > 0, C->aux);
+      e = launch_asm_rows((const float2 *)d_fields + ((size_t)c * T + t0) * field, S, tw, nf * height, width, C->aux);
+      for (uint32_t p0 = 0; p0 < n_planes && e == hipSuccess; p0 += group) {
+        const uint32_t np = std::min(group, n_planes - p0);
+        if (t0 == 0 || group < n_planes)   // else the tables of the channel are in place
+          for (uint32_t p = 0; p < np && e == hipSuccess; ++p)
+            e = launch_asm_transfer(H + p * h_elems, width, height,
+                                    asm_params(width, height, pitch, lambdas[c], distances[p0 + p], flags, na), C->aux);
+        if (e == hipSuccess) e = launch_asm_columns(S, A, H, np, tw, nf, width, height, C->aux);
+        float *I = (float *)d_out + ((size_t)c * n_planes + p0) * field;
+        if (e == hipSuccess) e = launch_asm_intensity(A, tw, np, nf, width, height, I, weight, t0 > 0, C->aux);
       }
     }
   }
@@ -1761,10 +1780,7 @@ hpt_status hpt_reconstruct(hpt_ctx *C, const void *d_fields, uint32_t n_ch, uint
   else (void)hipStreamSynchronize(C->aux);  // launches already queued still use the scratch
   {
     std::lock_guard<std::mutex> g(C->mu);
-    C->release(A, third);
-    C->release(B, third);
-    C->release(B0, third);
-    C->release(W, tw_bytes);
+    scratch_give(C, W);
   }
   if (e != hipSuccess) return fail(HPT_EDEVICE, std::string("reconstruction failed: ") + hipGetErrorString(e));
   return HPT_OK;
