@@ -1,12 +1,14 @@
 """Line FFTs of the propagation at the edges of every padded length, against
 the FP64 oracle: the shortest and the longest field that each padded length
 2 .. 8192 takes, along each axis; plane groups and transfer functions under a
-budget that has room for one at a time.
+budget that has room for one at a time; work buffers kept between calls.
 
 Bar: a path through the transforms has at most 2 log2 Px + 2 log2 Py <= 52
 butterfly levels, each rounding by at most 2^-24 of the RMS with random signs:
 52^0.5 x 6e-8 = 4e-7 x RMS, and the largest of up to 10^6 values lies within
 6 of that: 3e-6 x RMS; 1e-5 leaves room for the twiddles' own rounding."""
+import threading
+
 import numpy as np
 import pytest
 
@@ -116,3 +118,24 @@ def test_room_for_one_of_each(h, w):
     d = np.abs(np.angle(np.exp(1j * (ref[1].numpy().astype(np.float64) - phi_o))))
     assert np.percentile(d, 99.9) <= 1e-3
 
+
+def test_calls_of_several_threads_and_sizes(ctx):
+    """Work buffers are kept between calls: calls of changing sizes, one after
+    another and from four threads at once, give what each gives alone."""
+    jobs = [(64, 64, 1e-3), (300, 200, -2e-3), (31, 500, 5e-3), (200, 300, 4e-3)]
+    data = [_fields(3, h, w, seed=k) for k, (h, w, _) in enumerate(jobs)]
+    alone = [_asm(ctx, u, z) for u, (_, _, z) in zip(data, jobs)]
+    again = [_asm(ctx, u, z) for u, (_, _, z) in zip(data, jobs)]
+    wrong = []
+
+    def work(k):
+        for _ in range(20):
+            if not np.array_equal(_asm(ctx, data[k], jobs[k][2]), alone[k]):
+                wrong.append(k)
+
+    ts = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert all(np.array_equal(a, b) for a, b in zip(alone, again)) and not wrong
