@@ -36,7 +36,7 @@ hipError_t launch_cache_reduce(const BatchDev &B, hipStream_t st);
 // (added to the field; run after the batch's accumulation, on its stream).
 // max_pn: the largest pixel count of a unit in the batch.
 hipError_t launch_points(const BatchDev &B, uint32_t max_pn, hipStream_t st);
-hipError_t launch_grf(double2 *spec, double2 *rows, float2 *table, uint32_t gw, uint32_t gh, uint32_t T,
-                      uint64_t seed, double scale, hipStream_t st);
+hipError_t launch_grf(double2 *rows, float2 *table, uint32_t gw, uint32_t gh, uint32_t T, uint64_t seed, double scale,
+                      hipStream_t st);
 
 }  // namespace hpt

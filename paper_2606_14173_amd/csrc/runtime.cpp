@@ -247,16 +247,20 @@ Grf *find_grf(hpt_ctx *C, uint32_t gw, uint32_t gh, uint32_t T, uint64_t seed) {
 }
 
 size_t grf_table_bytes(uint32_t gw, uint32_t gh, uint32_t T) { return (size_t)gw * gh * T * sizeof(float2); }
-size_t grf_temp_bytes(uint32_t gw, uint32_t gh, uint32_t T) { return 2 * (size_t)gw * gh * T * sizeof(double2); }
+size_t grf_temp_bytes(uint32_t gw, uint32_t gh, uint32_t T) { return (size_t)gw * gh * T * sizeof(double2); }
 
+// Bins (sx, sy) with 4 (sx^2 gh^2 + sy^2 gw^2) <= gw^2 gh^2: the largest |sx|
+// only falls as |sy| grows, so both are walked once.
 uint64_t passband_bins(uint32_t gw, uint32_t gh) {
+  const int64_t w = gw, h = gh;
   uint64_t n = 0;
-  for (uint32_t jy = 0; jy < gh; ++jy) {
-    int64_t sy = jy < (gh + 1) / 2 ? (int64_t)jy : (int64_t)jy - gh;
-    for (uint32_t jx = 0; jx < gw; ++jx) {
-      int64_t sx = jx < (gw + 1) / 2 ? (int64_t)jx : (int64_t)jx - gw;
-      if (4 * (sx * sx * (int64_t)gh * gh + sy * sy * (int64_t)gw * gw) <= (int64_t)gw * gw * (int64_t)gh * gh) ++n;
-    }
+  int64_t m = w / 2;   // |sx| of the last row
+  for (int64_t sy = 0; sy <= h / 2; ++sy) {
+    while (m >= 0 && 4 * (m * m * h * h + sy * sy * w * w) > w * w * h * h) --m;
+    if (m < 0) break;
+    // signed bins [-m, m]; an even grid's Nyquist bin is -w/2 (or -h/2) only
+    const uint64_t row = (uint64_t)(2 * m + 1) - (2 * m == w ? 1 : 0);
+    n += row * (sy == 0 || 2 * sy == h ? 1 : 2);
   }
   return n;
 }
@@ -284,18 +288,16 @@ hpt_status build_grf(hpt_ctx *C, uint32_t gw, uint32_t gh, uint32_t T, uint64_t 
   if (C->used + tb + tmp > C->budget) return fail(HPT_EBUDGET, "random-phase table does not fit the budget");
   auto g = std::make_unique<Grf>();
   g->gw = gw; g->gh = gh; g->T = T; g->seed = seed; g->bytes = tb;
-  void *spec = nullptr, *rows = nullptr;
+  void *rows = nullptr;
   if (C->alloc((void **)&g->d, tb) != hipSuccess) return fail(HPT_ENOMEM, "table allocation failed");
-  if (C->alloc(&spec, tmp / 2) != hipSuccess || C->alloc(&rows, tmp / 2) != hipSuccess) {
-    C->release(spec, tmp / 2);
+  if (C->alloc(&rows, tmp) != hipSuccess) {
     C->release(g->d, tb);
     return fail(HPT_ENOMEM, "table scratch allocation failed");
   }
   double scale = 1.0 / std::sqrt((double)passband_bins(gw, gh));
-  hipError_t e = launch_grf((double2 *)spec, (double2 *)rows, g->d, gw, gh, T, seed, scale, st);
+  hipError_t e = launch_grf((double2 *)rows, g->d, gw, gh, T, seed, scale, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
-  C->release(spec, tmp / 2);
-  C->release(rows, tmp / 2);
+  C->release(rows, tmp);
   if (e != hipSuccess) {
     C->release(g->d, tb);
     return fail(HPT_EDEVICE, std::string("table build failed: ") + hipGetErrorString(e));
