@@ -189,7 +189,8 @@ static_assert(sizeof(PathRes) == 32, "PathRes is one 32-byte record");
 
 struct BatchDev {
   const UnitDev *units;
-  uint32_t n_units, n_paths, n_acc, lds_unused;
+  uint32_t n_units, n_paths, n_acc;
+  uint32_t dense;             // every queue is dense (see k_shade): no ordering passes, no index lists
   // per path slot
   unsigned long long *s_sig;  // final signature (debug records and signature sums only)
   int32_t *s_first;           // first hit (debug records only)

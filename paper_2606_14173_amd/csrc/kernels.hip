@@ -16,6 +16,8 @@
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "device.hpp"
 #include "kernels.hpp"
 
@@ -213,7 +215,6 @@ __device__ __forceinline__ void store_first(const RayQueue &Q, uint32_t k, const
 // coherence: every path keeps its slot.
 constexpr int kRaygenBlock = 1024;
 constexpr uint32_t kRaygenSlots = 8;                              // 2 and 4 sort less coherently
-constexpr uint32_t kRaygenWindow = kRaygenSlots * kRaygenBlock;  // slots a block sorts
 
 // A batch of one job with at most kLdsUnits units (and, for shading, a scene
 // of at most kLdsMats materials) has its descriptors copied to LDS once per
@@ -223,6 +224,12 @@ constexpr uint32_t kRaygenWindow = kRaygenSlots * kRaygenBlock;  // slots a bloc
 // every load in flight.)
 constexpr uint32_t kLdsMats = 64;
 constexpr uint32_t kLdsUnits = 128;
+// Batches of at most this many paths keep dense queues: their shading takes
+// entries with atomics and the two ordering launches of each interaction, 5 us
+// each however few the rays, are left out (a 64 x 64 job 134 -> 125 us). Up to
+// 2^21 paths both ways take the same time; 3.8M paths are 5 % slower with atomics.
+constexpr uint32_t kDensePaths = 1u << 18;
+constexpr uint32_t kRaygenSmall = 1u << 18;
 // Workgroups of a shading launch at most (a multiple of 8): each copies the
 // descriptors once and then walks its chunks of the queue.
 constexpr uint32_t kShadeGridMax = 32768;
@@ -386,8 +393,13 @@ __device__ __forceinline__ uint32_t sort_key(const UnitDev &U, const JobDev &J, 
   return key;
 }
 
-template <bool UNI>
+// SLOTS: slots per thread. A batch of at most kRaygenSmall paths, which would
+// be on less than an eighth of the CUs, takes one: 65536 paths 31 us on 8
+// workgroups, 8 us on 64 (a 64 x 64 job 150 -> 125 us); from there on the
+// better sort is worth as much.
+template <bool UNI, uint32_t SLOTS>
 __global__ void __launch_bounds__(kRaygenBlock) k_raygen(BatchDev B) {
+  constexpr uint32_t kRaygenWindow = SLOTS * kRaygenBlock;  // slots a block sorts
   static_assert(kSortBins <= kRaygenBlock, "one thread per sort bin");
   __shared__ uint32_t hist[kSortBins], wsum[kRaygenBlock / 64];
   __shared__ uint16_t perm[kRaygenWindow];
@@ -400,7 +412,11 @@ __global__ void __launch_bounds__(kRaygenBlock) k_raygen(BatchDev B) {
   __shared__ UnitDev lds_units[UNI ? kLdsUnits : 1];
   static_assert(kRaygenWindow <= 65536, "sorted positions fit 16 bits");
   const uint32_t g0 = blockIdx.x * kRaygenWindow;
-  if (blockIdx.x == 0 && threadIdx.x == 0) { B.counters[0] = B.n_paths; B.counters[1] = 0; }
+  if (blockIdx.x == 0) {  // counters and traversal claims of a new batch
+    if (threadIdx.x < 8) B.counters[threadIdx.x] = threadIdx.x == 0 ? B.n_paths : 0u;
+    static_assert(2 * kClaimClasses * kClaimStride <= kRaygenBlock, "one thread per claim word");
+    if (threadIdx.x < 2 * kClaimClasses * kClaimStride) B.claims[threadIdx.x] = 0;
+  }
   if (threadIdx.x < kSortBins) hist[threadIdx.x] = 0;
   if (UNI) {
     const uint32_t t = threadIdx.x;
@@ -412,9 +428,9 @@ __global__ void __launch_bounds__(kRaygenBlock) k_raygen(BatchDev B) {
   __syncthreads();
   const UnitDev *Us = UNI ? lds_units : B.units;
   const uint32_t nv = min(kRaygenWindow, B.n_paths - g0);  // slots of this block
-  uint32_t key[kRaygenSlots], rank[kRaygenSlots];
+  uint32_t key[SLOTS], rank[SLOTS];
 #pragma unroll
-  for (uint32_t r = 0; r < kRaygenSlots; ++r) {
+  for (uint32_t r = 0; r < SLOTS; ++r) {
     const uint32_t w = r * blockDim.x + threadIdx.x, i = g0 + w;
     key[r] = 0;
     rank[r] = 0;
@@ -450,7 +466,7 @@ __global__ void __launch_bounds__(kRaygenBlock) k_raygen(BatchDev B) {
   if (threadIdx.x < kSortBins) hist[threadIdx.x] = before + inc - own;  // the bin's first sorted position
   __syncthreads();
 #pragma unroll
-  for (uint32_t r = 0; r < kRaygenSlots; ++r) {
+  for (uint32_t r = 0; r < SLOTS; ++r) {
     const uint32_t w = r * blockDim.x + threadIdx.x;
     if (w < nv) perm[hist[key[r]] + rank[r]] = (uint16_t)w;
   }
@@ -459,7 +475,7 @@ __global__ void __launch_bounds__(kRaygenBlock) k_raygen(BatchDev B) {
   // ray built again from what the first pass kept (a hologram path) or
   // generated again (a cache path), so that the queue entries are written in
   // order
-  for (uint32_t r = 0; r < kRaygenSlots; ++r) {
+  for (uint32_t r = 0; r < SLOTS; ++r) {
     const uint32_t w = r * blockDim.x + threadIdx.x;
     if (w >= nv) break;
     const uint32_t wi = perm[w], k = g0 + wi, u = s_unit[wi];
@@ -1017,7 +1033,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(EXT
   __shared__ SceneDev lds_scene[1];
   __shared__ MaterialDev lds_mats[UNI ? kLdsMats : 1];
   __shared__ UnitDev lds_units[UNI ? kLdsUnits : 1];
-  __shared__ uint32_t wave_cnt[kBlock / 64], wave_base[kBlock / 64 + 1];
+  __shared__ uint32_t wave_cnt[kBlock / 64], wave_base[kBlock / 64 + 1], chunk_base;
   uint32_t n = B.counters[q];
   int qo = q ^ 1;
   if (blockIdx.x == 0 && threadIdx.x < kClaimClasses)  // traversal claims of queue q
@@ -1056,7 +1072,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(EXT
     e.on = false;
     e.sig = false;
     if (live) {
-      const uint32_t i = FIRST ? v : B.Q[q].idx[v];
+      const uint32_t i = FIRST || B.dense ? v : B.Q[q].idx[v];
       // the hit record is requested first: it is the longest chain
       // (entry -> primitive -> record); the rest of the state is loaded
       // while it is in flight
@@ -1080,7 +1096,10 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(EXT
     // compaction within the chunk: the continuing rays of chunk c take
     // entries [256 c, 256 c + count) of the next queue in lane order (wave
     // counts from ballots, their prefix in LDS), and the count is recorded
-    // for the scan that orders the chunks; no atomic leaves the workgroup
+    // for the scan that orders the chunks; no atomic leaves the workgroup. In
+    // a batch with dense queues the chunk takes its entries with one atomic
+    // instead (the order of a queue changes nothing but coherence), which
+    // saves the two ordering launches
     unsigned long long m = __ballot(e.on);
     const uint32_t lane = __lane_id(), wv = threadIdx.x / 64u;
     if (lane == 0) wave_cnt[wv] = (uint32_t)__popcll(m);
@@ -1088,11 +1107,12 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(EXT
     if (threadIdx.x == 0) {
       uint32_t tot = 0;
       for (uint32_t k = 0; k < kBlock / 64; ++k) { wave_base[k] = tot; tot += wave_cnt[k]; }
-      B.Q[qo].cnt[c] = tot;
+      if (B.dense) chunk_base = tot ? atomicAdd(&B.counters[qo], tot) : 0u;
+      else { B.Q[qo].cnt[c] = tot; chunk_base = c * kBlock; }
     }
     __syncthreads();
     const uint32_t before = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-    if (e.on) stage_store<EXT>(G, B.Q[qo], c * kBlock + wave_base[wv] + before, e.sig);
+    if (e.on) stage_store<EXT>(G, B.Q[qo], chunk_base + wave_base[wv] + before, e.sig);
   }
 }
 
@@ -1649,13 +1669,15 @@ static inline uint32_t grid_for(uint64_t n) { return (uint32_t)((n + kBlock - 1)
 static inline uint32_t round8(uint32_t g) { return (g + 7u) & ~7u; }
 
 hipError_t launch_raygen(const BatchDev &B, bool uni, hipStream_t st) {
-  uint32_t g = (uint32_t)(((uint64_t)B.n_paths + kRaygenWindow - 1) / kRaygenWindow);
-  if (uni)
-    hipLaunchKernelGGL(k_raygen<true>, dim3(g), dim3(kRaygenBlock), 0, st, B);
-  else
-    hipLaunchKernelGGL(k_raygen<false>, dim3(g), dim3(kRaygenBlock), 0, st, B);
+  const uint32_t slots = B.n_paths <= kRaygenSmall ? 1u : kRaygenSlots, window = slots * kRaygenBlock;
+  const uint32_t g = (uint32_t)(((uint64_t)B.n_paths + window - 1) / window);
+  auto k = slots == 1 ? (uni ? k_raygen<true, 1> : k_raygen<false, 1>)
+                      : (uni ? k_raygen<true, kRaygenSlots> : k_raygen<false, kRaygenSlots>);
+  hipLaunchKernelGGL(k, dim3(g), dim3(kRaygenBlock), 0, st, B);
   return hipGetLastError();
 }
+
+bool dense_queues(uint32_t n_paths) { return n_paths <= kDensePaths; }
 
 uint32_t trace_grid(uint32_t n_paths) {
   // enough waves to fill every CU; waves beyond the resident ones find the
@@ -1740,21 +1762,22 @@ static GrfRadices grf_radices(uint32_t n) {
   return F;
 }
 
-// Lines of n values a workgroup takes, and the LDS they need beside the roots.
-static uint32_t grf_per(uint32_t n) {
-  uint32_t c = kGrfValues / n;
+// Lines of n values a workgroup takes of `lines`: as many as its registers and
+// LDS (beside the roots) hold, but no more than leave each CU a workgroup.
+static uint32_t grf_per(uint32_t n, uint32_t lines) {
+  uint32_t c = std::min({kGrfValues / n, 32u, std::max(1u, lines / 256u)});
   while (c > 1 && (n + (size_t)c * grf_pitch(n)) * sizeof(double2) > kGrfLds) --c;
-  return c < 32 ? c : 32;
+  return c;
 }
-static size_t grf_lds_bytes(uint32_t n) { return (n + (size_t)grf_per(n) * grf_pitch(n)) * sizeof(double2); }
+static size_t grf_lds_bytes(uint32_t n, uint32_t per) { return (n + (size_t)per * grf_pitch(n)) * sizeof(double2); }
 
 hipError_t launch_grf(double2 *rows, float2 *table, uint32_t gw, uint32_t gh, uint32_t T, uint64_t seed, double scale,
                       hipStream_t st) {
   if (gw < 1 || gh < 1 || gw > 4096 || gh > 4096) return hipErrorInvalidValue;
-  const uint32_t pr = grf_per(gw), pc = grf_per(gh), groups = ((gw + pc - 1) / pc + 7) / 8 * 8;
-  hipLaunchKernelGGL(k_grf_rows, dim3((T * gh + pr - 1) / pr), dim3(kGrfBlock), grf_lds_bytes(gw), st, rows, gw, gh,
+  const uint32_t pr = grf_per(gw, T * gh), pc = grf_per(gh, T * gw), groups = ((gw + pc - 1) / pc + 7) / 8 * 8;
+  hipLaunchKernelGGL(k_grf_rows, dim3((T * gh + pr - 1) / pr), dim3(kGrfBlock), grf_lds_bytes(gw, pr), st, rows, gw, gh,
                      T * gh, pr, seed, grf_radices(gw));
-  hipLaunchKernelGGL(k_grf_cols, dim3(groups * T), dim3(kGrfBlock), grf_lds_bytes(gh), st, rows, table, gw, gh, T, pc,
+  hipLaunchKernelGGL(k_grf_cols, dim3(groups * T), dim3(kGrfBlock), grf_lds_bytes(gh, pc), st, rows, table, gw, gh, T, pc,
                      scale, grf_radices(gh));
   return hipGetLastError();
 }

@@ -7,6 +7,8 @@
 namespace hpt {
 
 // uni: the batch has one job and at most shade_lds_units() units
+// Whether a batch of n_paths keeps dense queues (BatchDev::dense).
+bool dense_queues(uint32_t n_paths);
 hipError_t launch_raygen(const BatchDev &B, bool uni, hipStream_t st);
 // One interaction for every ray in queue q: closest hit (trace), then
 // shading that compacts continuing rays into queue q^1 (shade).

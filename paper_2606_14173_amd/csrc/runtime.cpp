@@ -49,6 +49,7 @@ double ms_between(Clock::time_point a, Clock::time_point b) {
 }
 
 constexpr uint32_t kMaxUnitsPerBatch = 4096;
+constexpr size_t kJobDevsKept = 64;
 // per path, in two sets: final signature, first hit, results; per queue
 // entry (two queues): state (32 B), FP64 prefix ray (56 B), FP32 ray (32 B),
 // hit (8 B), index list (4 B; chunk counts and offsets: 8 B per 256 entries)
@@ -161,6 +162,7 @@ struct hpt_ctx {
   std::deque<Job *> queue;     // submitted, not yet admitted
   std::vector<Job *> running;  // admitted, units left
   std::vector<std::unique_ptr<Grf>> grfs;
+  std::vector<JobDev *> job_devs;  // device descriptors of released jobs, for the next ones
   // batch buffers: queues, counters and stack spill shared by consecutive
   // batches (one stream runs their tracing in order); per-path results and
   // unit tables in two sets, so that batch k's accumulation (on its own
@@ -355,7 +357,8 @@ void free_job_buffers(hpt_ctx *C, Job *J) {
   C->release(J->rec, J->n_rec * sizeof(hpt_path_record));
   C->release(J->contrib, J->n_contrib * sizeof(float2));
   C->release(J->sigsum, J->n_sig * sizeof(unsigned long long));
-  C->release(J->dev, sizeof(JobDev));
+  if (J->dev && C->job_devs.size() < kJobDevsKept) C->job_devs.push_back(J->dev);
+  else C->release(J->dev, sizeof(JobDev));
   J->field = nullptr; J->rec = nullptr; J->contrib = nullptr; J->sigsum = nullptr; J->dev = nullptr;
   if (J->ready) { (void)hipEventDestroy(J->ready); J->ready = nullptr; }
 }
@@ -389,7 +392,8 @@ hpt_status admit(hpt_ctx *C, Job *J) {
   if (J->n_rec) ok &= C->alloc((void **)&J->rec, J->n_rec * sizeof(hpt_path_record)) == hipSuccess;
   if (J->n_contrib) ok &= C->alloc((void **)&J->contrib, J->n_contrib * sizeof(float2)) == hipSuccess;
   if (J->n_sig) ok &= C->alloc((void **)&J->sigsum, J->n_sig * sizeof(unsigned long long)) == hipSuccess;
-  ok &= C->alloc((void **)&J->dev, sizeof(JobDev)) == hipSuccess;
+  if (!C->job_devs.empty()) { J->dev = C->job_devs.back(); C->job_devs.pop_back(); }
+  else ok &= C->alloc((void **)&J->dev, sizeof(JobDev)) == hipSuccess;
   if (!ok) {
     free_job_buffers(C, J);
     if (J->grf) { J->grf->users--; J->grf = nullptr; }
@@ -408,8 +412,8 @@ hpt_status admit(hpt_ctx *C, Job *J) {
   if (e == hipSuccess && J->contrib) e = hipMemsetAsync(J->contrib, 0, J->n_contrib * sizeof(float2), C->stream);
   if (e == hipSuccess && J->sigsum)
     e = hipMemsetAsync(J->sigsum, 0, J->n_sig * sizeof(unsigned long long), C->stream);
+  // (J->host stays as it is until the job is released: no wait for the copy)
   if (e == hipSuccess) e = hipMemcpyAsync(J->dev, &J->host, sizeof(JobDev), hipMemcpyHostToDevice, C->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(C->stream);
   if (e != hipSuccess) {
     free_job_buffers(C, J);
     return fail(HPT_EDEVICE, std::string("job set-up failed: ") + hipGetErrorString(e));
@@ -483,25 +487,31 @@ void timed_launch(hpt_ctx::Slot &L, int kind, hipStream_t st, hipError_t &e, F &
 // next batch starts beside its first kAccParts traversal launches, so that
 // the gather-heavy accumulation runs beside the ALU-bound tracing rather
 // than beside the memory-bound ray generation or the latency-bound shading.
+//
+// With no batch to run beside (after null) what is left runs as one launch,
+// behind the batch's last shading pass on its own stream: the host has
+// waited for the batch before, whose accumulation added to the same fields.
 hipError_t launch_accumulation(hpt_ctx *C, int si, hipEvent_t after, uint32_t part_end) {
   hpt_ctx::Slot &L = C->slots[si];
-  hipError_t e = hipStreamWaitEvent(C->acc, L.ev_shade, 0);
-  if (e == hipSuccess && after) e = hipStreamWaitEvent(C->acc, after, 0);
-  const BatchDev &B = L.B;
-  for (; e == hipSuccess && L.acc_parts < part_end; ++L.acc_parts) {
-    const uint32_t lo = (uint32_t)((uint64_t)B.n_acc * L.acc_parts / kAccParts);
-    const uint32_t hi = (uint32_t)((uint64_t)B.n_acc * (L.acc_parts + 1) / kAccParts);
-    if (L.has_holo)
-      timed_launch(L, HPT_K_ACCUMULATE, C->acc, e,
-                   [&] { return launch_accumulate(B, L.has_f64, L.has_f32, lo, hi, C->acc); });
+  hipStream_t S = after ? C->acc : C->stream;
+  hipError_t e = hipSuccess;
+  if (after) {
+    e = hipStreamWaitEvent(S, L.ev_shade, 0);
+    if (e == hipSuccess) e = hipStreamWaitEvent(S, after, 0);
   }
+  const BatchDev &B = L.B;
+  const uint32_t lo = (uint32_t)((uint64_t)B.n_acc * L.acc_parts / kAccParts);
+  const uint32_t hi = (uint32_t)((uint64_t)B.n_acc * part_end / kAccParts);
+  if (L.has_holo)
+    timed_launch(L, HPT_K_ACCUMULATE, S, e, [&] { return launch_accumulate(B, L.has_f64, L.has_f32, lo, hi, S); });
+  if (e == hipSuccess) L.acc_parts = part_end;
   if (L.acc_parts < kAccParts) return e;
   L.acc_pending = false;
   // point-emitter terms: on the same stream after the accumulation, so that
   // every read-modify-write of a pixel's field is ordered
-  if (e == hipSuccess && L.pts_max_pn) e = launch_points(B, L.pts_max_pn, C->acc);
-  if (L.has_cache) timed_launch(L, HPT_K_CACHE_REDUCE, C->acc, e, [&] { return launch_cache_reduce(B, C->acc); });
-  if (e == hipSuccess) e = hipEventRecord(L.ev_done, C->acc);
+  if (e == hipSuccess && L.pts_max_pn) e = launch_points(B, L.pts_max_pn, S);
+  if (L.has_cache) timed_launch(L, HPT_K_CACHE_REDUCE, S, e, [&] { return launch_cache_reduce(B, S); });
+  if (e == hipSuccess) e = hipEventRecord(L.ev_done, S);
   return e;
 }
 
@@ -551,13 +561,12 @@ hpt_status launch_batch(hpt_ctx *C, int si, int prev) {
   B.n_units = (uint32_t)P.size();
   B.n_paths = slot;
   B.n_acc = acc;
+  B.dense = dense_queues(slot) ? 1u : 0u;
   const uint32_t profile = L.profile;
   L.ne = 0;
   hipError_t e = hipSuccess;
   hipStream_t S = C->stream;
   e = hipMemcpyAsync(L.d_units, L.h_units, P.size() * sizeof(UnitDev), hipMemcpyHostToDevice, S);
-  if (e == hipSuccess) e = hipMemsetAsync(B.counters, 0, 8 * sizeof(uint32_t), S);
-  if (e == hipSuccess) e = hipMemsetAsync(B.claims, 0, 2 * kClaimClasses * kClaimStride * sizeof(uint32_t), S);
   if (e == hipSuccess && profile >= 2) e = hipMemsetAsync(B.work, 0, 2 * sizeof(unsigned long long), S);
   if (e == hipSuccess) e = hipEventRecord(L.ev0, S);
   timed_launch(L, HPT_K_RAYGEN, S, e,
@@ -569,11 +578,11 @@ hpt_status launch_batch(hpt_ctx *C, int si, int prev) {
                    B.n_units <= shade_lds_units();
   for (uint32_t it = 0; it <= max_b; ++it) {
     int q = (int)(it & 1u);
-    timed_launch(L, HPT_K_TRACE, S, e, [&] { return launch_trace(B, q, it == 0, profile >= 2, S); });
+    timed_launch(L, HPT_K_TRACE, S, e, [&] { return launch_trace(B, q, it == 0 || B.dense, profile >= 2, S); });
     timed_launch(L, HPT_K_SHADE, S, e, [&] { return launch_shade(B, q, it, L.has_ext, uni, S); });
     // the last pass ends every path (interaction max_b + 1 exceeds the
     // budget), so only the earlier ones leave rays to order
-    if (it < max_b) timed_launch(L, HPT_K_COMPACT, S, e, [&] { return launch_compact(B, q, S); });
+    if (it < max_b && !B.dense) timed_launch(L, HPT_K_COMPACT, S, e, [&] { return launch_compact(B, q, S); });
     // part it + 1 of the previous batch's accumulation starts beside this
     // batch's next traversal (all that is left after the last such pass)
     if (it + 1 < kAccParts && e == hipSuccess && prev >= 0 && C->slots[prev].acc_pending) {
@@ -905,6 +914,7 @@ void hpt_destroy(hpt_ctx *C) {
   for (auto &kv : C->jobs) free_job_buffers(C, kv.second.get());
   for (auto &g : C->grfs) (void)hipFree(g->d);
   if (C->idle.p) (void)hipFree(C->idle.p);
+  for (JobDev *p : C->job_devs) (void)hipFree(p);
   for (auto &kv : C->scenes) {
     for (void *p : kv.second->bufs) (void)hipFree(p);
     (void)hipFree(kv.second->dev);
