@@ -266,4 +266,78 @@ bool build_bvh(const float *tri, uint32_t n_tri, const float *sph, uint32_t n_sp
   return out.max_depth < kBvhDepthMax;
 }
 
+namespace {
+
+// Bits of the smallest binary16 >= v for v >= 0 (never subnormal), of the
+// largest <= v otherwise.
+uint16_t half_up(double v) {
+  if (v == 0.0) return 0;
+  if (v > 65504.0) return 0x7C00;
+  int e;
+  std::frexp(v, &e);               // v in [2^(e-1), 2^e)
+  if (e - 1 < -14) return 0x0400;  // 2^-14
+  uint32_t m = (uint32_t)std::ceil(std::ldexp(v, 11 - e));  // [1024, 2048]
+  if (m == 2048) { m = 1024; ++e; }
+  return e - 1 > 15 ? 0x7C00 : (uint16_t)(((e + 14) << 10) | (m - 1024));
+}
+uint16_t half_below(double v) {
+  if (v == 0.0) return 0x8000;
+  if (v > 65504.0) return std::isinf(v) ? 0x7C00 : 0x7BFF;
+  int e;
+  std::frexp(v, &e);
+  if (e - 1 < -14) return 0;
+  return (uint16_t)(((e + 14) << 10) | ((uint32_t)std::floor(std::ldexp(v, 11 - e)) - 1024));
+}
+uint16_t half_floor(double v) { return v >= 0 ? half_below(v) : (uint16_t)(0x8000 | half_up(-v)); }
+uint16_t half_ceil(double v) { return v >= 0 ? half_up(v) : (uint16_t)(0x8000 | half_below(-v)); }
+
+}  // namespace
+
+void pack_nodes(const BvhResult &bvh, PackedNodes &out) {
+  const size_t n = bvh.n_nodes;
+  // largest coordinate and half extent of the scene: the children of the
+  // root hold everything (an empty child's planes are infinite)
+  double mag = 0.0, half = 0.0;
+  static const int kAxis[3][4] = {{0, 1, 4, 5}, {2, 3, 6, 7}, {8, 9, 10, 11}};
+  for (int a = 0; a < 3 && n; ++a) {
+    double lo = INFINITY, hi = -INFINITY;
+    for (int k : kAxis[a]) {
+      const double p = bvh.nodes[k];
+      if (std::isfinite(p)) { lo = std::min(lo, p); hi = std::max(hi, p); }
+    }
+    if (lo > hi) continue;
+    mag = std::max({mag, std::fabs(lo), std::fabs(hi)});
+    half = std::max(half, 0.5 * (hi - lo));
+  }
+  int e = 0;
+  std::frexp(std::max(half, 1e-30), &e);            // half < 2^e
+  const int sh = std::min(std::max(14 - e, -100), 100);
+  out.scale = (float)std::ldexp(1.0, sh);
+  const double S = std::ldexp(1.0, sh);
+  // planes move outwards by 2^-21 of the largest coordinate too: what the
+  // traversal's rounding of (origin - o) / d can be off by
+  const double margin = S * mag * 4.76837158203125e-07;
+  out.words.assign(12 * n, 0u);
+  for (size_t i = 0; i < n; ++i) {
+    const float *p = &bvh.nodes[16 * i];
+    uint32_t *w = &out.words[12 * i];
+    double org[3];
+    for (int a = 0; a < 3; ++a) {
+      double lo = INFINITY, hi = -INFINITY;
+      for (int k : kAxis[a])
+        if (std::isfinite(p[k])) { lo = std::min(lo, (double)p[k]); hi = std::max(hi, (double)p[k]); }
+      const float o = lo <= hi ? (float)(0.5 * (lo + hi) * S) : 0.f;
+      std::memcpy(&w[a], &o, 4);
+      org[a] = o;
+    }
+    std::memcpy(&w[3], &p[12], 4);
+    for (int c = 0; c < 2; ++c)
+      for (int a = 0; a < 3; ++a) {
+        const double lo = p[kAxis[a][2 * c]] * S - org[a] - margin, hi = p[kAxis[a][2 * c + 1]] * S - org[a] + margin;
+        w[4 + 3 * c + a] = (uint32_t)half_floor(lo) | (uint32_t)half_ceil(hi) << 16;
+      }
+    std::memcpy(&w[10], &p[13], 4);
+  }
+}
+
 }  // namespace hpt

@@ -6,7 +6,7 @@
 namespace hpt {
 
 constexpr uint32_t kBvhDepthMax = 64;   // traversal stack entries
-constexpr uint32_t kBvhTopNodes = 256;  // nodes stored first, in breadth-first order from the root
+constexpr uint32_t kBvhTopNodes = 320;  // nodes stored first, in breadth-first order from the root
 
 struct BvhResult {
   std::vector<float> nodes;   // 16 floats per node
@@ -20,5 +20,19 @@ struct BvhResult {
 // (global ids). Returns false if the input is empty, too large, or the
 // tree is deeper than the traversal stack.
 bool build_bvh(const float *tri, uint32_t n_tri, const float *sph, uint32_t n_sph, BvhResult &out);
+
+// The nodes as the traversal reads them, 12 words (48 bytes) each: origin xyz
+// (float) and link 0; the planes of both child boxes as pairs of binary16
+// offsets from the origin (child 0: lo.x hi.x, lo.y hi.y, lo.z hi.z, then child
+// 1), rounded outwards; link 1; unused. Origin and offsets are in units of 1 /
+// scale, a power of two for which every offset is below 2^15. The traversal is
+// bound by vector-L1 accesses (one per lane and load) and by vector
+// instructions: such a node takes three loads instead of four, and a fused
+// multiply-add reads a binary16 offset for nothing.
+struct PackedNodes {
+  std::vector<uint32_t> words;
+  float scale = 1.f;
+};
+void pack_nodes(const BvhResult &bvh, PackedNodes &out);
 
 }  // namespace hpt

@@ -70,6 +70,7 @@ struct Hit { float t; int32_t prim; };
 // Read-only scene data addressed as global memory (address space 1), so the
 // compiler issues global loads (counted by vmcnt only) rather than flat loads.
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v3f __attribute__((ext_vector_type(3)));
 typedef const v4f __attribute__((address_space(1))) *GF4;
 __device__ __forceinline__ GF4 as_global(const float4 *p) { return (GF4)(const void *)p; }
 __device__ __forceinline__ float4 ld4(GF4 p) {
@@ -101,12 +102,13 @@ struct RayPre {
   F3 o, d;
   int kx, ky, kz;
   float Sx, Sy, Sz;
-  F3 inv;
+  F3 inv;   // reciprocal direction over the node scale (slab tests)
 };
 
 __device__ __forceinline__ float comp(F3 v, int k) { return k == 0 ? v.x : (k == 1 ? v.y : v.z); }
 
-__device__ __forceinline__ RayPre ray_pre(F3 o, F3 d) {
+// scale: of the scene's packed nodes.
+__device__ __forceinline__ RayPre ray_pre(F3 o, F3 d, float scale) {
   RayPre r;
   r.o = o; r.d = d;
   float ax = fabsf(d.x), ay = fabsf(d.y), az = fabsf(d.z);
@@ -118,9 +120,12 @@ __device__ __forceinline__ RayPre ray_pre(F3 o, F3 d) {
   float dz = comp(d, kz);
   r.Sx = comp(d, kx) / dz; r.Sy = comp(d, ky) / dz; r.Sz = 1.0f / dz;
   // reciprocal direction for the slab tests; zero components become huge
-  r.inv.x = 1.0f / (fabsf(d.x) > 1e-30f ? d.x : copysignf(1e-30f, d.x));
-  r.inv.y = 1.0f / (fabsf(d.y) > 1e-30f ? d.y : copysignf(1e-30f, d.y));
-  r.inv.z = 1.0f / (fabsf(d.z) > 1e-30f ? d.z : copysignf(1e-30f, d.z));
+  // (bounded, so that an offset of 0 times it is 0)
+  const float is = 1.0f / scale;  // exact: a power of two
+  auto slab = [&](float c) {
+    return __builtin_amdgcn_fmed3f(1.0f / (fabsf(c) > 1e-30f ? c : copysignf(1e-30f, c)) * is, -1e36f, 1e36f);
+  };
+  r.inv = f3(slab(d.x), slab(d.y), slab(d.z));
   return r;
 }
 
@@ -170,21 +175,71 @@ __device__ __forceinline__ bool sph_hit(const RayPre &r, F3 c, float rad, float 
   return true;
 }
 
-__device__ __forceinline__ void box2(const RayPre &r, float4 a, float4 b, float4 c, float tmin,
+// fmaxf and fminf of values that are never signalling NaNs (the compiler would
+// quieten a loop-carried operand with an instruction of its own each time).
+__device__ __forceinline__ float max_num(float a, float b) {
+  float r;
+  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ float min_num(float a, float b) {
+  float r;
+  asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+
+// Lanes in a mask (as a scalar: the compiler would compare it as 64 bits).
+__device__ __forceinline__ int count_lanes(uint64_t mask) {
+  int n;
+  asm("s_bcnt1_i32_b64 %0, %1" : "=s"(n) : "s"(mask) : "scc");
+  return n;
+}
+
+// One BVH node as the traversal reads it (three 16-byte words; see
+// pack_nodes): origin and link 0; plane offsets; plane offsets and link 1.
+struct NodeWords { float4 a, b; v3f c; };
+
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+
+// What the slab tests of one ray share: its origin in node units times r.inv
+// (negated) and, per axis, 16 where the ray runs downwards: rotating a plane
+// pair by that puts the plane it meets first into the low half.
+struct Slabs {
+  float ox, oy, oz;
+  uint32_t sx, sy, sz;
+};
+__device__ __forceinline__ Slabs slabs_of(const RayPre &r, float scale) {
+  Slabs s;
+  s.ox = -(r.o.x * scale * r.inv.x); s.oy = -(r.o.y * scale * r.inv.y); s.oz = -(r.o.z * scale * r.inv.z);
+  s.sx = __float_as_uint(r.inv.x) >> 27 & 16u;
+  s.sy = __float_as_uint(r.inv.y) >> 27 & 16u;
+  s.sz = __float_as_uint(r.inv.z) >> 27 & 16u;
+  return s;
+}
+
+// Distances (in ray parameters) at which the ray enters and leaves the slab
+// between the planes at offsets w = (lo, hi) from the node's origin, which it
+// reaches at t = c: fused multiply-adds on the binary16 offsets.
+__device__ __forceinline__ void planes(float w, uint32_t swap, float inv, float c, float &near, float &far) {
+  const uint32_t u = __float_as_uint(w);
+  const h2 p = __builtin_bit_cast(h2, __builtin_amdgcn_alignbit(u, u, swap));
+  near = fmaf((float)p.x, inv, c);
+  far = fmaf((float)p.y, inv, c);
+}
+
+// Entry distances t0, t1 and hits h0, h1 of the node's children for ray r.
+__device__ __forceinline__ void box2(const RayPre &r, const Slabs &s, const NodeWords &n, float tmin,
                                      float tmax, float &t0, float &t1, bool &h0, bool &h1) {
-  float ox = r.o.x * r.inv.x, oy = r.o.y * r.inv.y, oz = r.o.z * r.inv.z;
-  float l0x = a.x * r.inv.x - ox, h0x = a.y * r.inv.x - ox;
-  float l0y = a.z * r.inv.y - oy, h0y = a.w * r.inv.y - oy;
-  float l1x = b.x * r.inv.x - ox, h1x = b.y * r.inv.x - ox;
-  float l1y = b.z * r.inv.y - oy, h1y = b.w * r.inv.y - oy;
-  float l0z = c.x * r.inv.z - oz, h0z = c.y * r.inv.z - oz;
-  float l1z = c.z * r.inv.z - oz, h1z = c.w * r.inv.z - oz;
-  float n0 = fmaxf(fmaxf(fminf(l0x, h0x), fminf(l0y, h0y)), fmaxf(fminf(l0z, h0z), tmin));
-  float f0 = fminf(fminf(fmaxf(l0x, h0x), fmaxf(l0y, h0y)), fminf(fmaxf(l0z, h0z), tmax));
-  float n1 = fmaxf(fmaxf(fminf(l1x, h1x), fminf(l1y, h1y)), fmaxf(fminf(l1z, h1z), tmin));
-  float f1 = fminf(fminf(fmaxf(l1x, h1x), fmaxf(l1y, h1y)), fminf(fmaxf(l1z, h1z), tmax));
+  const float cx = fmaf(n.a.x, r.inv.x, s.ox), cy = fmaf(n.a.y, r.inv.y, s.oy), cz = fmaf(n.a.z, r.inv.z, s.oz);
+  float nx, fx, ny, fy, nz, fz;
+  planes(n.b.x, s.sx, r.inv.x, cx, nx, fx); planes(n.b.y, s.sy, r.inv.y, cy, ny, fy);
+  planes(n.b.z, s.sz, r.inv.z, cz, nz, fz);
+  const float n0 = max_num(fmaxf(fmaxf(nx, ny), nz), tmin), f0 = min_num(fminf(fminf(fx, fy), fz), tmax);
+  planes(n.b.w, s.sx, r.inv.x, cx, nx, fx); planes(n.c.x, s.sy, r.inv.y, cy, ny, fy);
+  planes(n.c.y, s.sz, r.inv.z, cz, nz, fz);
+  const float n1 = max_num(fmaxf(fmaxf(nx, ny), nz), tmin), f1 = min_num(fminf(fminf(fx, fy), fz), tmax);
   // slack of a few ulp so that rounding in the slabs never culls a hit
-  h0 = n0 <= f0 * 1.0000004f; h1 = n1 <= f1 * 1.0000004f;
+  h0 = n0 <= f0 * 1.0000007f; h1 = n1 <= f1 * 1.0000007f;
   t0 = n0; t1 = n1;
 }
 
@@ -213,6 +268,13 @@ __device__ __forceinline__ void leaf_test(const RayPre &r, GF4 P, int32_t node, 
   }
 }
 
+// A scene's BVH in global memory.
+struct Bvh {
+  GF4 N, P;          // packed nodes, primitive records
+  uint32_t n_nodes;
+  float scale;       // node units per metre
+};
+
 // Traversal state of one lane: closest hit in (tmin, inf), ties to the
 // lower global id, skipping the triangle `exclude`. The stack lives in LDS,
 // one column per lane (consecutive entries `stride` ints apart, so lanes
@@ -226,12 +288,13 @@ struct Trav {
   Hit best;
 };
 constexpr int32_t kDone = 0x7FFFFFFF;
+constexpr int32_t kPop = 0x7FFFFFFE;   // the next node is the top of the stack
 
-__device__ __forceinline__ void trav_init(Trav &T, F3 o, F3 d, float tmin, int32_t exclude, bool empty) {
-  T.r = ray_pre(o, d);
-  T.tmin = tmin * 1.0f + 0.0f;  // an arithmetic result: no canonicalisation in the loop
+__device__ __forceinline__ void trav_init(Trav &T, F3 o, F3 d, float tmin, int32_t exclude, const Bvh &V) {
+  T.r = ray_pre(o, d, V.scale);
+  T.tmin = tmin;
   T.exclude = exclude;
-  T.node = empty ? kDone : 0;
+  T.node = V.n_nodes == 0 ? kDone : 0;
   T.sp = 0;
   T.best.t = INFINITY;
   T.best.prim = -1;
@@ -257,12 +320,12 @@ struct Stack {
 };
 
 __device__ __forceinline__ void st_store(const Stack &S, int j, int32_t v) {
-  if (j < kStackLds) S.lds[j * S.stride] = v;
+  if (j < kStackLds) S.lds[j * (int)S.stride] = v;
   else S.spill[(size_t)(j - kStackLds) * S.sstride] = v;
 }
 
 __device__ __forceinline__ int32_t st_load(const Stack &S, int j) {
-  return j < kStackLds ? S.lds[j * S.stride] : S.spill[(size_t)(j - kStackLds) * S.sstride];
+  return j < kStackLds ? S.lds[j * (int)S.stride] : S.spill[(size_t)(j - kStackLds) * S.sstride];
 }
 
 __device__ __forceinline__ void push(const Stack &S, int &sp, int32_t v) {
@@ -270,26 +333,35 @@ __device__ __forceinline__ void push(const Stack &S, int &sp, int32_t v) {
   ++sp;
 }
 
+// Below the first entry of a lane's LDS column lies kDone (stack_floor), so
+// popping an empty stack needs no test.
 __device__ __forceinline__ int32_t pop(const Stack &S, int &sp) {
-  if (sp == 0) return kDone;
   --sp;
   return st_load(S, sp);
 }
+__device__ __forceinline__ void stack_floor(const Stack &S) { S.lds[-(int)S.stride] = kDone; }
 
 __device__ __forceinline__ float4 ld4l(LF4 p) {
   v4f v = *p;
   return make_float4(v.x, v.y, v.z, v.w);
 }
 
-// The four float4 of BVH node `node`: from LDS for the top levels.
-__device__ __forceinline__ void load_node(const Stack &S, GF4 N, int32_t node, float4 &a, float4 &b, float4 &c,
-                                          float4 &l) {
+// BVH node `node`: from LDS for the top levels.
+__device__ __forceinline__ NodeWords load_node(const Stack &S, GF4 N, int32_t node) {
+  NodeWords n;
   if ((uint32_t)node < S.n_nodes) {
-    a = ld4l(S.nodes + 4 * node); b = ld4l(S.nodes + 4 * node + 1);
-    c = ld4l(S.nodes + 4 * node + 2); l = ld4l(S.nodes + 4 * node + 3);
+    // a 24-bit product (the compiler takes the 32-bit one, a quarter as fast)
+    uint32_t off;
+    asm("v_mul_u32_u24 %0, 48, %1" : "=v"(off) : "v"(node));
+    const LF4 p = (LF4)((const char __attribute__((address_space(3))) *)S.nodes + off);
+    n.a = ld4l(p); n.b = ld4l(p + 1);
+    n.c = *(const v3f __attribute__((address_space(3))) *)(p + 2);
   } else {
-    a = ld4(N + 4 * node); b = ld4(N + 4 * node + 1); c = ld4(N + 4 * node + 2); l = ld4(N + 4 * node + 3);
+    const GF4 p = N + 3u * (uint32_t)node;
+    n.a = ld4(p); n.b = ld4(p + 1);
+    n.c = *(const v3f __attribute__((address_space(1))) *)(p + 2);
   }
+  return n;
 }
 
 // Advance this lane by one round: descend inner nodes, postponing the first
@@ -302,50 +374,40 @@ __device__ __forceinline__ void load_node(const Stack &S, GF4 N, int32_t node, f
 // make the result independent of the order. COUNT adds node visits and
 // primitive tests to nv / nt.
 template <bool COUNT>
-__device__ __forceinline__ void trav_step(Trav &T, GF4 N, GF4 P, const Stack &St, uint32_t &nv, uint32_t &nt) {
+__device__ __forceinline__ void trav_step(Trav &T, const Bvh &V, const Stack &St, uint32_t &nv, uint32_t &nt) {
+  const Slabs sl = slabs_of(T.r, V.scale);
   int32_t node = T.node;
   int sp = T.sp;
-  bool has_leaf = false;
-  int32_t leaf = 0;
+  int32_t leaf = 0;   // the postponed leaf; leaf links are negative
   for (;;) {
-    if (node >= 0 && node != kDone) {
+    if ((uint32_t)node < (uint32_t)kPop) {
       if (COUNT) ++nv;
-      float4 a, b, c, l4;
-      load_node(St, N, node, a, b, c, l4);
-      int32_t c0 = __float_as_int(l4.x), c1 = __float_as_int(l4.y);
+      const NodeWords n = load_node(St, V.N, node);
+      const int32_t c0 = __float_as_int(n.a.w), c1 = __float_as_int(n.c.z);
       float t0, t1;
       bool h0, h1;
-      box2(T.r, a, b, c, T.tmin, T.best.t, t0, t1, h0, h1);
-      if (h0 && h1) {
-        bool first0 = t0 <= t1;
-        push(St, sp, first0 ? c1 : c0);
-        node = first0 ? c0 : c1;
-      } else if (h0) {
-        node = c0;
-      } else if (h1) {
-        node = c1;
-      } else {
-        node = pop(St, sp);
-      }
+      box2(T.r, sl, n, T.tmin, T.best.t, t0, t1, h0, h1);
+      const bool first0 = (h0 ? t0 : INFINITY) <= (h1 ? t1 : INFINITY);
+      node = h0 || h1 ? (first0 ? c0 : c1) : kPop;
+      if (h0 && h1) push(St, sp, first0 ? c1 : c0);
     }
-    if (node < 0 && !has_leaf) {  // postpone the leaf, keep descending
-      has_leaf = true;
+    if ((node & ~leaf) < 0) {  // postpone the leaf, keep descending
       leaf = node;
-      node = pop(St, sp);
+      node = kPop;
     }
-    bool ready = has_leaf || node == kDone || node < 0;
+    if (node == kPop) node = pop(St, sp);
     // leave the descent once at most kTraceStragglers lanes are still
     // looking for a leaf (waiting for all of them leaves most of the wave
     // idle); the stragglers resume where they are in the next step
-    if (__popcll(__ballot(!ready)) <= kTraceStragglers) break;
+    const uint32_t looking = (uint32_t)node | ((uint32_t)leaf & 0x80000000u);
+    if (count_lanes(__builtin_amdgcn_ballot_w64(looking < (uint32_t)kPop)) <= kTraceStragglers) break;
   }
-  if (has_leaf) {
-    if (COUNT) nt += ((uint32_t)(~leaf) & 7u) + 1u;
-    leaf_test(T.r, P, leaf, T.tmin, T.exclude, T.best);
-  } else if (node < 0) {
-    if (COUNT) nt += ((uint32_t)(~node) & 7u) + 1u;
-    leaf_test(T.r, P, node, T.tmin, T.exclude, T.best);
-    node = pop(St, sp);
+  // the leaf to test now: the postponed one, or one just popped
+  const int32_t now = leaf < 0 ? leaf : node;
+  if (now < 0) {
+    if (COUNT) nt += ((uint32_t)(~now) & 7u) + 1u;
+    leaf_test(T.r, V.P, now, T.tmin, T.exclude, T.best);
+    if (leaf >= 0) node = pop(St, sp);
   }
   T.node = node;
   T.sp = sp;

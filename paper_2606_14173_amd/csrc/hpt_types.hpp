@@ -9,14 +9,14 @@ namespace hpt {
 
 constexpr int kMaxT = 64;
 constexpr int kStackMax = 64;        // BVH depth bound enforced by the builder
-// LDS per traversal workgroup: kStackLds x 256 entries of the stack plus
-// kLdsNodes 64-byte nodes (8 KB + 14 KB), so that seven workgroups share a
+// LDS per traversal workgroup: (1 + kStackLds) x 256 entries of the stack plus
+// kLdsNodes 48-byte nodes (9 KB + 13.5 KB), so that seven workgroups share a
 // CU's 160 KB at seven waves per SIMD
 #ifndef HPT_STACK_LDS
 #define HPT_STACK_LDS 8
 #endif
 #ifndef HPT_LDS_NODES
-#define HPT_LDS_NODES 224
+#define HPT_LDS_NODES 288
 #endif
 // top BVH nodes a traversal workgroup keeps in LDS (the builder stores the
 // first levels first; at most its kBvhTopNodes)
@@ -90,13 +90,13 @@ static_assert(sizeof(HitRec) == 64, "HitRec is one 64-byte record");
 
 // Device view of one resident scene.
 struct SceneDev {
-  const float4 *nodes;       // BVH2: 4 x float4 per node (two child boxes + links)
+  const float4 *nodes;       // BVH2: 3 x float4 per node (pack_nodes)
   const float4 *prims;       // 3 x float4 per primitive in leaf order
   const HitRec *hits;        // [n_sph + n_tri] in leaf order
   const MaterialDev *mats;
   uint32_t n_sph, n_tri, n_mat, n_nodes;
   float env[3];
-  uint32_t pad0;
+  float node_scale;
   // radiance cache
   const uint16_t *cache;     // [3][res^3][bins^2] binary16, or null
   uint32_t cache_res, cache_bins;

@@ -499,6 +499,20 @@ __global__ void __launch_bounds__(kRaygenBlock) k_raygen(BatchDev B) {
   }
 }
 
+__device__ __forceinline__ Bvh bvh_of(const SceneDev &S) {
+  return {as_global(S.nodes), as_global(S.prims), S.n_nodes, S.node_scale};
+}
+
+// The same for a scene that every lane of the wave shares, in scalar registers.
+__device__ __forceinline__ Bvh shared_bvh_of(const SceneDev &S) {
+  auto one = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
+  auto ptr = [&](const float4 *p) {
+    const uint64_t a = (uint64_t)p;
+    return as_global((const float4 *)((uint64_t)one((uint32_t)(a >> 32)) << 32 | one((uint32_t)a)));
+  };
+  return {ptr(S.nodes), ptr(S.prims), one(S.n_nodes), __uint_as_float(one(__float_as_uint(S.node_scale)))};
+}
+
 // ------------------------------------------------------------------ trace
 // FP32 closest hit for every ray of queue q (rays in order: entries 0..n-1
 // of the dense first queue, else the entries idx lists). The queue is cut into chunks of
@@ -512,24 +526,30 @@ __global__ void __launch_bounds__(kRaygenBlock) k_raygen(BatchDev B) {
 // queue is drained, however short the queue. The grid is a multiple of
 // kClaimClasses workgroups, so every class is drained.
 // The traversal stack is kStackLds entries per lane in LDS, then the lane's
-// column of the global spill. Seven waves per SIMD (72 VGPRs, a few spilled
-// to scratch outside the node loop) hide more of the node-fetch latency than
-// six with no spill.
-template <bool COUNT>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))) k_trace(BatchDev B, int q, int dense) {
+// column of the global spill. Seven waves per SIMD (72 VGPRs) hide more of the
+// node-fetch latency than six. ONE: every ray of the batch traverses
+// B.scene_uniform, whose BVH is then held in scalar registers (in vector ones
+// six were spilled) and its first nodes in LDS.
+// Bound by vector instructions (85 % of the cycles) and by vector-L1 accesses
+// (89 %, one per lane and load, half of the lanes): 48-byte nodes for 64-byte
+// ones, and a third fewer instructions per node, took the 1M-triangle scene's
+// 1920x1080 RGB T = 24 hologram from 691 to 635 ms and its 512x512 one from
+// 25.6 to 23.4 ms.
+template <bool COUNT, bool ONE>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(ONE && !COUNT ? 7 : 6))) k_trace(BatchDev B, int q, int dense) {
   // issue priority over the previous batch's accumulation waves that share
   // the SIMDs (the traversal is on the step's critical path, the
   // accumulation beside it is not)
   __builtin_amdgcn_s_setprio(HPT_TRACE_PRIO);
-  __shared__ int32_t stack[kStackLds * kBlock];
-  __shared__ v4f top_nodes[4 * (kLdsNodes ? kLdsNodes : 1)];
+  __shared__ int32_t stack[(1 + kStackLds) * kBlock];   // the first row: see stack_floor
+  __shared__ v4f top_nodes[ONE ? 3 * kLdsNodes : 1];
   // the top levels of the BVH (its first kLdsNodes nodes) in LDS, when every
   // ray of the batch traverses the same scene
-  const uint32_t n_top = (kLdsNodes && B.scene_uniform) ? min(kLdsNodes, B.scene_uniform->n_nodes) : 0u;
-  if (n_top) {
-    const GF4 src = as_global(B.scene_uniform->nodes);
-    for (uint32_t k = threadIdx.x; k < 4 * n_top; k += blockDim.x) {
-      const float4 v = ld4(src + k);
+  Bvh V = ONE ? shared_bvh_of(*B.scene_uniform) : Bvh{};
+  const uint32_t n_top = ONE ? min(kLdsNodes, V.n_nodes) : 0u;
+  if (ONE) {
+    for (uint32_t k = threadIdx.x; k < 3 * n_top; k += blockDim.x) {
+      const float4 v = ld4(V.N + k);
       top_nodes[k] = v4f{v.x, v.y, v.z, v.w};
     }
     __syncthreads();
@@ -543,17 +563,15 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))
   uint32_t *claim = B.claims + ((uint32_t)q * kClaimClasses + cls) * kClaimStride;
   const uint32_t n_chunks = (n + kTraceChunk - 1) / kTraceChunk;
   const uint32_t lane = __lane_id();
-  const Stack St{(LdsI32)(stack + threadIdx.x), kBlock,
+  const Stack St{(LdsI32)(stack + kBlock + threadIdx.x), kBlock,
                  (GlbI32)(B.stack_spill + xcd_block() * blockDim.x + threadIdx.x), B.spill_threads,
                  (LF4)top_nodes, n_top};
+  stack_floor(St);
   uint32_t nv = 0, nt = 0;
   uint32_t next = 0, end = 0;  // unassigned entries of the wave's chunk
   bool more = true;            // the queue may hold unclaimed entries
-  int64_t i = -1;              // queue entry of this lane's ray, -1: none
+  int32_t i = -1;              // queue entry of this lane's ray, -1: none
   Trav T;
-  const SceneDev *S = B.scene_uniform;
-  GF4 N = as_global(S ? S->nodes : nullptr), P = as_global(S ? S->prims : nullptr);
-  uint32_t nn = S ? S->n_nodes : 0;
   for (;;) {
     if (more && next >= end && __any(i < 0)) {  // claim the next chunk
       uint32_t k = 0;
@@ -573,13 +591,10 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))
         uint32_t k = next + (uint32_t)__popcll(need & ((1ull << lane) - 1ull));
         if (k < end) {
           if (!dense) k = B.Q[q].idx[k];   // the k-th ray of a compacted queue
-          i = k;
-          if (!B.scene_uniform) {
-            S = B.units[B.Q[q].unit[k]].scene;
-            N = as_global(S->nodes); P = as_global(S->prims); nn = S->n_nodes;
-          }
+          i = (int32_t)k;
+          if (!ONE) V = bvh_of(*B.units[B.Q[q].unit[k]].scene);
           float4 r0 = B.Q[q].ray[2 * k], r1 = B.Q[q].ray[2 * k + 1];
-          trav_init(T, f3(r0.x, r0.y, r0.z), f3(r1.x, r1.y, r1.z), r0.w, __float_as_int(r1.w), nn == 0);
+          trav_init(T, f3(r0.x, r0.y, r0.z), f3(r1.x, r1.y, r1.z), r0.w, __float_as_int(r1.w), V);
         }
       }
       next = min(end, next + (uint32_t)__popcll(need));
@@ -589,7 +604,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7))
       continue;
     }
     if (i >= 0) {
-      if (T.node != kDone) trav_step<COUNT>(T, N, P, St, nv, nt);
+      if (T.node != kDone) trav_step<COUNT>(T, V, St, nv, nt);
       if (T.node == kDone) {
         B.Q[q].t[i] = T.best.t;
         B.Q[q].prim[i] = T.best.prim;
@@ -824,11 +839,11 @@ __device__ float next_event(const SceneDev &S, const MaterialDev *M, const Mater
   float c = 0.f;
   if (cos_y > 0.f && e.fcos > 0.f) {
     Trav T;
-    trav_init(T, x, om, kTmin, gid >= (int32_t)S.n_sph ? gid : -1, S.n_nodes == 0);
+    const Bvh V = bvh_of(S);
+    trav_init(T, x, om, kTmin, gid >= (int32_t)S.n_sph ? gid : -1, V);
     T.best.t = dist * (1.0f - 1e-4f);
-    const GF4 N = as_global(S.nodes), P = as_global(S.prims);
     uint32_t nv = 0, nt = 0;
-    while (T.node != kDone && T.best.prim < 0) trav_step<false>(T, N, P, St, nv, nt);
+    while (T.node != kDone && T.best.prim < 0) trav_step<false>(T, V, St, nv, nt);
     vis = T.best.prim < 0;
     if (vis) {
       const float pl = dist * dist / (cos_y * (float)S.light_area);
@@ -1028,7 +1043,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(EXT
   // FIRST: queue 0 as ray generation wrote it (dense); else a compacted
   // queue, read through its index list
   __shared__ StageLds G;
-  __shared__ int32_t nee_stack[EXT ? kStackLds * kBlock : 1];
+  __shared__ int32_t nee_stack[EXT ? (1 + kStackLds) * kBlock : 1];
   __shared__ JobDev lds_job[1];
   __shared__ SceneDev lds_scene[1];
   __shared__ MaterialDev lds_mats[UNI ? kLdsMats : 1];
@@ -1049,8 +1064,9 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(EXT
   const uint32_t cstep = EXT ? gridDim.x : gridDim.x / 8u;
   const uint32_t cend = EXT ? nb8 : (b % 8u + 1u) * per;
   if (c0 >= cend || c0 * blockDim.x >= n) return;  // no entries for this workgroup
-  const Stack St{(LdsI32)(nee_stack + (EXT ? threadIdx.x : 0u)), kBlock,
+  const Stack St{(LdsI32)(nee_stack + (EXT ? kBlock + threadIdx.x : 0u)), kBlock,
                  (GlbI32)(B.stack_spill + blockIdx.x * blockDim.x + threadIdx.x), B.spill_threads, nullptr, 0u};
+  if (EXT) stack_floor(St);
   if (UNI) {
     const uint32_t t = threadIdx.x;
     const uint32_t *jsrc = (const uint32_t *)B.job_uniform, *ssrc = (const uint32_t *)B.scene_uniform;
@@ -1377,18 +1393,20 @@ __global__ void __launch_bounds__(kBlock) k_accumulate(BatchDev B, uint32_t lane
 constexpr int kPtsBlock = 64;
 __device__ bool segment_blocked(const SceneDev &S, F3 o, F3 d, float tmax, int32_t *st) {
   if (S.n_nodes == 0) return false;
-  const RayPre r = ray_pre(o, d);
+  const float scale = S.node_scale;
+  const RayPre r = ray_pre(o, d, scale);
   const GF4 N = as_global(S.nodes), P = as_global(S.prims);
+  const Slabs sl = slabs_of(r, scale);
   int32_t node = 0;
   int sp = 0;
   for (;;) {
     if (node >= 0) {
-      const float4 a = ld4(N + 4 * node), b = ld4(N + 4 * node + 1), c = ld4(N + 4 * node + 2),
-                   l4 = ld4(N + 4 * node + 3);
+      const Stack none{nullptr, 0u, nullptr, 0u, nullptr, 0u};
+      const NodeWords w = load_node(none, N, node);
       float t0, t1;
       bool h0, h1;
-      box2(r, a, b, c, kTmin, tmax, t0, t1, h0, h1);
-      const int32_t c0 = __float_as_int(l4.x), c1 = __float_as_int(l4.y);
+      box2(r, sl, w, kTmin, tmax, t0, t1, h0, h1);
+      const int32_t c0 = __float_as_int(w.a.w), c1 = __float_as_int(w.c.z);
       if (h0 && h1) {
         st[sp * kPtsBlock] = t0 <= t1 ? c1 : c0;
         ++sp;
@@ -1693,8 +1711,9 @@ uint32_t trace_block() { return kBlock; }
 hipError_t launch_trace(const BatchDev &B, int q, bool dense, bool count, hipStream_t st) {
   uint32_t g = trace_grid(B.n_paths);
   if ((uint64_t)g * kBlock > B.spill_threads) return hipErrorInvalidValue;
-  if (count) hipLaunchKernelGGL(k_trace<true>, dim3(g), dim3(kBlock), 0, st, B, q, dense ? 1 : 0);
-  else hipLaunchKernelGGL(k_trace<false>, dim3(g), dim3(kBlock), 0, st, B, q, dense ? 1 : 0);
+  auto k = count ? (B.scene_uniform ? k_trace<true, true> : k_trace<true, false>)
+                 : (B.scene_uniform ? k_trace<false, true> : k_trace<false, false>);
+  hipLaunchKernelGGL(k, dim3(g), dim3(kBlock), 0, st, B, q, dense ? 1 : 0);
   return hipGetLastError();
 }
 

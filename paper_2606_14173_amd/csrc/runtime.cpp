@@ -992,6 +992,8 @@ hpt_status hpt_scene_upload(hpt_ctx *C, const hpt_scene_desc *d, uint64_t *out) 
   uint32_t n = d->n_tri + d->n_sph;
   if (n > 0 && !build_bvh(d->tri, d->n_tri, d->sph, d->n_sph, bvh))
     return fail(HPT_EINVAL, "BVH build failed (tree deeper than the traversal stack)");
+  PackedNodes packed;
+  if (n > 0) pack_nodes(bvh, packed);
   // bounds in FP64 from the float32 data (the radiance-cache grid uses them)
   for (int a = 0; a < 3; ++a) { S->lo[a] = INFINITY; S->hi[a] = -INFINITY; }
   for (uint32_t i = 0; i < d->n_sph; ++i)
@@ -1074,7 +1076,7 @@ hpt_status hpt_scene_upload(hpt_ctx *C, const hpt_scene_desc *d, uint64_t *out) 
     pts[2 * i] = make_float4(p[0], p[1], p[2], 0.f);
     pts[2 * i + 1] = make_float4(p[3], p[4], p[5], 0.f);
   }
-  size_t need = bvh.nodes.size() * 4 + bvh.prims.size() * 4 + sizeof(HitRec) * hits.size() +
+  size_t need = packed.words.size() * 4 + bvh.prims.size() * 4 + sizeof(HitRec) * hits.size() +
                 sizeof(MaterialDev) * mats.size() + sizeof(SceneDev) + sizeof(float4) * lights.size() +
                 sizeof(double) * light_cdf.size() + sizeof(float4) * pts.size();
   if (C->used + need > C->budget) make_room(C, need);
@@ -1090,7 +1092,7 @@ hpt_status hpt_scene_upload(hpt_ctx *C, const hpt_scene_desc *d, uint64_t *out) 
   SceneDev &h = S->host;
   std::memset(&h, 0, sizeof(h));
   if (n > 0) {
-    ok &= put(bvh.nodes.data(), bvh.nodes.size() * 4, &p); h.nodes = (const float4 *)p;
+    ok &= put(packed.words.data(), packed.words.size() * 4, &p); h.nodes = (const float4 *)p;
     ok &= put(bvh.prims.data(), bvh.prims.size() * 4, &p); h.prims = (const float4 *)p;
     ok &= put(hits.data(), sizeof(HitRec) * hits.size(), &p); h.hits = (const HitRec *)p;
   }
@@ -1106,6 +1108,7 @@ hpt_status hpt_scene_upload(hpt_ctx *C, const hpt_scene_desc *d, uint64_t *out) 
   for (uint32_t i = 0; i < d->n_mat; ++i)
     if (d->mat_type[i] == HPT_PRINCIPLED) S->principled = true;
   h.n_sph = d->n_sph; h.n_tri = d->n_tri; h.n_mat = d->n_mat; h.n_nodes = n ? bvh.n_nodes : 0;
+  h.node_scale = packed.scale;
   for (int c = 0; c < 3; ++c) h.env[c] = d->env[c];
   ok &= C->alloc((void **)&S->dev, sizeof(SceneDev)) == hipSuccess;
   if (ok) S->bytes += sizeof(SceneDev);
