@@ -120,10 +120,11 @@ __device__ __forceinline__ RayPre ray_pre(F3 o, F3 d, float scale) {
   float dz = comp(d, kz);
   r.Sx = comp(d, kx) / dz; r.Sy = comp(d, ky) / dz; r.Sz = 1.0f / dz;
   // reciprocal direction for the slab tests; zero components become huge
-  // (bounded, so that an offset of 0 times it is 0)
+  // (bounded, so that an offset of 0 times it is 0; the hardware reciprocal,
+  // good to an ulp, is within the slack of box2)
   const float is = 1.0f / scale;  // exact: a power of two
   auto slab = [&](float c) {
-    return __builtin_amdgcn_fmed3f(1.0f / (fabsf(c) > 1e-30f ? c : copysignf(1e-30f, c)) * is, -1e36f, 1e36f);
+    return __builtin_amdgcn_fmed3f(__builtin_amdgcn_rcpf(fabsf(c) > 1e-30f ? c : copysignf(1e-30f, c)) * is, -1e36f, 1e36f);
   };
   r.inv = f3(slab(d.x), slab(d.y), slab(d.z));
   return r;
@@ -239,7 +240,7 @@ __device__ __forceinline__ void box2(const RayPre &r, const Slabs &s, const Node
   planes(n.c.y, s.sz, r.inv.z, cz, nz, fz);
   const float n1 = max_num(fmaxf(fmaxf(nx, ny), nz), tmin), f1 = min_num(fminf(fminf(fx, fy), fz), tmax);
   // slack of a few ulp so that rounding in the slabs never culls a hit
-  h0 = n0 <= f0 * 1.0000007f; h1 = n1 <= f1 * 1.0000007f;
+  h0 = n0 <= f0 * 1.000001f; h1 = n1 <= f1 * 1.000001f;
   t0 = n0; t1 = n1;
 }
 

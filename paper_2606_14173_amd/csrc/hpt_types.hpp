@@ -38,6 +38,13 @@ constexpr int kTraceChunk = HPT_TRACE_CHUNK;  // queue entries a traversal wave 
 #endif
 constexpr uint32_t kTraceGridMax = HPT_TRACE_GRID;  // traversal workgroups per launch (8 per CU)
 constexpr int kTraceStragglers = HPT_STRAGGLERS;    // lanes a wave's descent stops waiting for
+#ifndef HPT_REFILL
+#define HPT_REFILL 16
+#endif
+// idle lanes a traversal wave waits for before it takes new rays: 1 / 8 / 16 /
+// 24 / 32 take 630 / 629 / 625 / 629 / 633 ms for a 1920x1080 RGB T = 24
+// hologram, 23.1 / 23.1 / 23.0 / 23.2 / 23.5 for a 512x512 one
+constexpr int kTraceRefill = HPT_REFILL;
 #ifndef HPT_CLAIM_CLASSES
 #define HPT_CLAIM_CLASSES 8
 #endif

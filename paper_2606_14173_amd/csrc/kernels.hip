@@ -534,9 +534,10 @@ __device__ __forceinline__ Bvh shared_bvh_of(const SceneDev &S) {
 // (89 %, one per lane and load, half of the lanes): 48-byte nodes for 64-byte
 // ones, and a third fewer instructions per node, took the 1M-triangle scene's
 // 1920x1080 RGB T = 24 hologram from 691 to 635 ms and its 512x512 one from
-// 25.6 to 23.4 ms.
+// 25.6 to 23.4 ms. (A mixed batch's top nodes, shared out in LDS, gained it
+// nothing.)
 template <bool COUNT, bool ONE>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(ONE && !COUNT ? 7 : 6))) k_trace(BatchDev B, int q, int dense) {
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(COUNT ? 6 : 7))) k_trace(BatchDev B, int q, int dense) {
   // issue priority over the previous batch's accumulation waves that share
   // the SIMDs (the traversal is on the step's critical path, the
   // accumulation beside it is not)
@@ -584,9 +585,12 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(ONE
         end = min(n, next + (uint32_t)kTraceChunk);
       }
     }
-    // refill idle lanes from the chunk, in lane order
-    unsigned long long need = __ballot(i < 0 && next < end);
-    if (need) {
+    // refill idle lanes from the chunk, in lane order, once kTraceRefill of
+    // them are idle (setting a ray up costs the wave the same for one lane as
+    // for all), the chunk's last rays are due or no ray is left
+    const unsigned long long need = __ballot(i < 0 && next < end);
+    const int idle = count_lanes(need);
+    if (idle >= kTraceRefill || (need && (end - next <= (uint32_t)kTraceRefill || !__any(i >= 0)))) {
       if (i < 0) {
         uint32_t k = next + (uint32_t)__popcll(need & ((1ull << lane) - 1ull));
         if (k < end) {
@@ -597,7 +601,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(ONE
           trav_init(T, f3(r0.x, r0.y, r0.z), f3(r1.x, r1.y, r1.z), r0.w, __float_as_int(r1.w), V);
         }
       }
-      next = min(end, next + (uint32_t)__popcll(need));
+      next = min(end, next + (uint32_t)idle);
     }
     if (!__any(i >= 0)) {
       if (!more) break;

@@ -82,6 +82,8 @@ int main(int argc, char **argv) {
       float inv[3], oi[3];
       for (int a = 0; a < 3; ++a) {
         inv[a] = 1.0f / (std::fabs(r.d[a]) > 1e-30f ? r.d[a] : std::copysign(1e-30f, r.d[a])) * (1.0f / pk.scale);
+        // (the hardware reciprocal may be an ulp off, either way)
+        if ((k + a) % 3 < 2) inv[a] = std::nextafter(inv[a], (k + a) % 3 ? INFINITY : -INFINITY);
         inv[a] = std::fmin(std::fmax(inv[a], -1e36f), 1e36f);
         oi[a] = -(r.o[a] * pk.scale * inv[a]);
       }
@@ -116,7 +118,7 @@ int main(int argc, char **argv) {
           }
           int32_t link;
           std::memcpy(&link, &w[c ? 10 : 3], 4);
-          if (near <= far * 1.0000007f) st.push_back(link);
+          if (near <= far * 1.000001f) st.push_back(link);
         }
       }
       hits += best < INFINITY;
