@@ -139,6 +139,20 @@ struct RayState {
   double ell;
 };
 
+// The occlusion query of a tail ray's light sample, which the traversal of the
+// ray's queue answers after the ray itself: from the ray's origin along d, up to
+// tmax; 0: none. It lies where a prefix ray has its FP64 ray: d and tmax in ox
+// and oy, the throughput and the light's contribution in oz, and the sample's
+// signature word in dx. The traversal adds their product to the entry's
+// radiance, and sets tmax to kVisible, where nothing is hit.
+struct Shadow { F3 d; float tmax; };
+constexpr float kVisible = INFINITY;
+__device__ __forceinline__ Shadow shadow_of(const RayQueue &Q, uint32_t k) {
+  const float2 a = ((const float2 *)Q.ox)[k], b = ((const float2 *)Q.oy)[k];
+  return {f3(a.x, a.y, b.x), b.y};
+}
+__device__ __forceinline__ uint32_t *shadow_sig(const RayQueue &Q, uint32_t k) { return (uint32_t *)(Q.dx + k); }
+
 // The path signature is carried only for jobs that keep per-path records
 // or signature sums (sig); the others never read it.
 template <bool EXT>
@@ -155,6 +169,10 @@ __device__ __forceinline__ void load_state(const RayQueue &Q, uint32_t i, RaySta
   r.beta = tail ? Q.beta[i] : 1.f;
   r.L = tail ? Q.L[i] : 0.f;
   r.pdf = (EXT && tail) ? Q.pdf[i] : 0.f;
+  if (EXT && sig && tail) {   // the light sample of the interaction that made the ray
+    const float s = shadow_of(Q, i).tmax;
+    if (s > 0.f) sig_add(r.sig, *shadow_sig(Q, i) | (s == kVisible ? 0x800000u : 0u));
+  }
   if ((r.meta & 1u) == STAGE_PREFIX) {
     r.o = D3{Q.ox[i], Q.oy[i], Q.oz[i]};
     r.d = D3{Q.dx[i], Q.dy[i], Q.dz[i]};
@@ -536,7 +554,7 @@ __device__ __forceinline__ Bvh shared_bvh_of(const SceneDev &S) {
 // 1920x1080 RGB T = 24 hologram from 691 to 635 ms and its 512x512 one from
 // 25.6 to 23.4 ms. (A mixed batch's top nodes, shared out in LDS, gained it
 // nothing.)
-template <bool COUNT, bool ONE>
+template <bool COUNT, bool ONE, bool NEE>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(COUNT ? 6 : 7))) k_trace(BatchDev B, int q, int dense) {
   // issue priority over the previous batch's accumulation waves that share
   // the SIMDs (the traversal is on the step's critical path, the
@@ -572,6 +590,10 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(COU
   uint32_t next = 0, end = 0;  // unassigned entries of the wave's chunk
   bool more = true;            // the queue may hold unclaimed entries
   int32_t i = -1;              // queue entry of this lane's ray, -1: none
+  // NEE: the limit of the entry's occlusion query, < 0 while that is under way;
+  // waits: the ray is done, the query to be set up
+  float ts = 0.f;
+  bool waits = false;
   Trav T;
   for (;;) {
     if (more && next >= end && __any(i < 0)) {  // claim the next chunk
@@ -587,32 +609,63 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(COU
     }
     // refill idle lanes from the chunk, in lane order, once kTraceRefill of
     // them are idle (setting a ray up costs the wave the same for one lane as
-    // for all), the chunk's last rays are due or no ray is left
+    // for all), the chunk's last rays are due or no ray is left; lanes whose
+    // occlusion query is next count as idle
     const unsigned long long need = __ballot(i < 0 && next < end);
-    const int idle = count_lanes(need);
-    if (idle >= kTraceRefill || (need && (end - next <= (uint32_t)kTraceRefill || !__any(i >= 0)))) {
-      if (i < 0) {
-        uint32_t k = next + (uint32_t)__popcll(need & ((1ull << lane) - 1ull));
-        if (k < end) {
-          if (!dense) k = B.Q[q].idx[k];   // the k-th ray of a compacted queue
-          i = (int32_t)k;
-          if (!ONE) V = bvh_of(*B.units[B.Q[q].unit[k]].scene);
-          float4 r0 = B.Q[q].ray[2 * k], r1 = B.Q[q].ray[2 * k + 1];
-          trav_init(T, f3(r0.x, r0.y, r0.z), f3(r1.x, r1.y, r1.z), r0.w, __float_as_int(r1.w), V);
+    const unsigned long long todo = NEE ? need | __ballot(waits) : need;
+    const int idle = count_lanes(todo);
+    if (idle >= kTraceRefill || (need && end - next <= (uint32_t)kTraceRefill) || (NEE && todo && !more) ||
+        (todo && !__any(i >= 0 && !(NEE && waits)))) {
+      const uint32_t k = next + (uint32_t)__popcll(need & ((1ull << lane) - 1ull));
+      const bool fresh = i < 0 && k < end;
+      if (fresh || (NEE && waits)) {
+        if (fresh) {
+          i = (int32_t)(dense ? k : B.Q[q].idx[k]);   // the k-th ray of a compacted queue
+          if (!ONE) V = bvh_of(*B.units[B.Q[q].unit[i]].scene);
+        }
+        const float4 r0 = B.Q[q].ray[2 * i], r1 = B.Q[q].ray[2 * i + 1];
+        F3 d = f3(r1.x, r1.y, r1.z);
+        float tmin = r0.w;
+        if (NEE) {
+          const Shadow s = shadow_of(B.Q[q], i);
+          if (fresh) ts = (B.Q[q].slot[i] >> kSlotBits & 1u) == STAGE_TAIL ? s.tmax : 0.f;
+          else { d = s.d; tmin = kTmin; }
+        }
+        trav_init(T, f3(r0.x, r0.y, r0.z), d, tmin, __float_as_int(r1.w), V);
+        if (NEE) {
+          if (!fresh) { T.best.t = ts; ts = -1.f; }
+          else if (tmin < 0.f) T.node = kDone;   // an absorbed path: only its query is left
+          waits = false;
         }
       }
-      next = min(end, next + (uint32_t)idle);
+      next = min(end, next + (uint32_t)count_lanes(need));
     }
     if (!__any(i >= 0)) {
       if (!more) break;
       continue;
     }
-    if (i >= 0) {
+    if (i >= 0 && !(NEE && waits)) {
+      const uint32_t nv0 = nv, nt0 = nt;
       if (T.node != kDone) trav_step<COUNT>(T, V, St, nv, nt);
+      const bool query = NEE && ts < 0.f;
+      if (query) {
+        nv = nv0; nt = nt0;   // (counted are the rays)
+        if (T.best.prim >= 0) T.node = kDone;
+      }
       if (T.node == kDone) {
-        B.Q[q].t[i] = T.best.t;
-        B.Q[q].prim[i] = T.best.prim;
-        i = -1;
+        if (query) {
+          if (T.best.prim < 0) {
+            const float2 w = ((const float2 *)B.Q[q].oz)[i];
+            B.Q[q].L[i] = fmaf(w.x, w.y, B.Q[q].L[i]);
+            ((float2 *)B.Q[q].oy)[i].y = kVisible;
+          }
+          i = -1;
+        } else {
+          B.Q[q].t[i] = T.best.t;
+          B.Q[q].prim[i] = T.best.prim;
+          if (NEE && ts > 0.f) waits = true;
+          else i = -1;
+        }
       }
     }
   }
@@ -643,6 +696,11 @@ struct StageLds {
   float rox[kBlock], roy[kBlock], roz[kBlock], rdx[kBlock], rdy[kBlock], rdz[kBlock];
   int32_t excl[kBlock];
 };
+// A staged tail ray's occlusion query (see Shadow): tmax 0: none.
+struct ShadowLds {
+  float dx[kBlock], dy[kBlock], dz[kBlock], tmax[kBlock], beta[kBlock], c[kBlock];
+  uint32_t sig[kBlock];
+};
 
 __device__ __forceinline__ void stage_put(StageLds &G, const RayState &r, F3 o, F3 d, int32_t excl, Emit &e) {
   const uint32_t t = threadIdx.x;
@@ -663,7 +721,8 @@ __device__ __forceinline__ void stage_put(StageLds &G, const RayState &r, F3 o, 
 // Entry k of queue Q from this lane's staged ray (the signature only if
 // its job reads signatures).
 template <bool EXT>
-__device__ __forceinline__ void stage_store(const StageLds &G, const RayQueue &Q, uint32_t k, bool sig) {
+__device__ __forceinline__ void stage_store(const StageLds &G, const ShadowLds &H, const RayQueue &Q, uint32_t k,
+                                            bool sig) {
   const uint32_t t = threadIdx.x, meta = G.meta[t];
   Q.slot[k] = G.slot[t] | ((meta & 1u) << kSlotBits) | (((meta >> 7) & 31u) << (kSlotBits + 1));
   Q.unit[k] = G.unit[t];
@@ -671,14 +730,25 @@ __device__ __forceinline__ void stage_store(const StageLds &G, const RayQueue &Q
   Q.bpre[k] = G.bpre[t]; Q.wt[k] = G.wt[t];
   if ((meta & 1u) == STAGE_TAIL) {  // a prefix ray's are 1 and 0
     Q.beta[k] = G.beta[t]; Q.L[k] = G.L[t];
-    if (EXT) Q.pdf[k] = G.pdf[t];
+    if (EXT) {
+      Q.pdf[k] = G.pdf[t];
+      const float tmax = H.tmax[t];
+      ((float2 *)Q.oy)[k] = make_float2(H.dz[t], tmax);
+      if (tmax > 0.f) {
+        ((float2 *)Q.ox)[k] = make_float2(H.dx[t], H.dy[t]);
+        ((float2 *)Q.oz)[k] = make_float2(H.beta[t], H.c[t]);
+        if (sig) *shadow_sig(Q, k) = H.sig[t];
+      }
+    }
   }
   if ((meta & 1u) == STAGE_PREFIX) {
     Q.ox[k] = G.ox[t]; Q.oy[k] = G.oy[t]; Q.oz[k] = G.oz[t];
     Q.dx[k] = G.dx[t]; Q.dy[k] = G.dy[t]; Q.dz[k] = G.dz[t];
     Q.ell[k] = G.ell[t];
   }
-  Q.ray[2 * k] = make_float4(G.rox[t], G.roy[t], G.roz[t], kTmin);
+  // a path that was absorbed and waits for its query has no ray: tmin < 0
+  const bool gone = EXT && (meta & 1u) == STAGE_TAIL && G.pdf[t] < 0.f;
+  Q.ray[2 * k] = make_float4(G.rox[t], G.roy[t], G.roz[t], gone ? -1.f : kTmin);
   Q.ray[2 * k + 1] = make_float4(G.rdx[t], G.rdy[t], G.rdz[t], __int_as_float(G.excl[t]));
 }
 
@@ -822,11 +892,12 @@ __device__ __forceinline__ void image_point(const BatchDev &B, const RayQueue &Q
 // gid, reached along d_in): an emitter triangle chosen with probability
 // proportional to area, a point uniform on it; its unoccluded one-sided
 // emission times f cos over the light pdf dist^2 / (cos_y A_total), with
-// the power-heuristic weight against the lobe pdf. The occlusion query is a
-// traversal of the whole BVH limited to the segment (stack St). The light
-// index and visibility enter the signature.
-__device__ float next_event(const SceneDev &S, const MaterialDev *M, const MaterialDev &m, uint32_t comp, F3 x,
-                            F3 d_in, F3 ng, int32_t gid, U4 w, const Stack &St, unsigned long long &sig) {
+// the power-heuristic weight against the lobe pdf, is c if the segment of
+// length tmax along d is free (tmax 0: nothing to add). The light index and
+// visibility enter the signature, with word sig.
+struct LightSample { F3 d; float tmax, c; uint32_t sig; };
+__device__ __forceinline__ LightSample next_event(const SceneDev &S, const MaterialDev *M, const MaterialDev &m,
+                                                  uint32_t comp, F3 x, F3 d_in, F3 ng, U4 w) {
   const auto cdf = glb(S.light_cdf);
   const double u0 = ud(w.x) * S.light_area;
   uint32_t lo = 0, hi = S.n_lights;  // first light whose running area exceeds u0
@@ -845,26 +916,16 @@ __device__ float next_event(const SceneDev &S, const MaterialDev *M, const Mater
   om = (1.0f / dist) * om;
   const float cos_y = -dot(om, f3(nn.x, nn.y, nn.z));
   const BsdfEval e = eval_lobe<true>(m, comp, d_in, ng, om);
-  bool vis = false;
-  float c = 0.f;
+  LightSample s{om, 0.f, 0.f, 0x60000000u | li};
   if (cos_y > 0.f && e.fcos > 0.f) {
-    Trav T;
-    const Bvh V = bvh_of(S);
-    trav_init(T, x, om, kTmin, gid >= (int32_t)S.n_sph ? gid : -1, V);
-    T.best.t = dist * (1.0f - 1e-4f);
-    uint32_t nv = 0, nt = 0;
-    while (T.node != kDone && T.best.prim < 0) trav_step<false>(T, V, St, nv, nt);
-    vis = T.best.prim < 0;
-    if (vis) {
-      const float pl = dist * dist / (cos_y * (float)S.light_area);
-      const float wl = pl * pl / (pl * pl + e.pdf * e.pdf);
-      const MaterialDev &lm = M[__float_as_uint(nn.w)];
-      const float le = comp == 0 ? lm.emit[0] : (comp == 1 ? lm.emit[1] : lm.emit[2]);
-      c = le * e.fcos * wl / pl;
-    }
+    s.tmax = dist * (1.0f - 1e-4f);
+    const float pl = dist * dist / (cos_y * (float)S.light_area);
+    const float wl = pl * pl / (pl * pl + e.pdf * e.pdf);
+    const MaterialDev &lm = M[__float_as_uint(nn.w)];
+    const float le = comp == 0 ? lm.emit[0] : (comp == 1 ? lm.emit[1] : lm.emit[2]);
+    s.c = le * e.fcos * wl / pl;
   }
-  sig_add(sig, 0x60000000u | (vis ? 0x800000u : 0u) | li);
-  return c;
+  return s;
 }
 
 template <bool EXT>
@@ -873,7 +934,7 @@ __device__ __forceinline__ void tail_interaction(const BatchDev &B, const RayQue
                                                  const MaterialDev *M, RayState &st, F3 x, F3 d_in,
                                                  const HitRec &H, uint32_t b, uint32_t bP, uint32_t comp,
                                                  uint32_t stream, float beta, float L,
-                                                 unsigned long long sig, float t_seg, const Stack *St,
+                                                 unsigned long long sig, float t_seg, ShadowLds &Sh,
                                                  Emit &e) {
   const int32_t gid = H.gid;
   const MaterialDev &m = M[H.mat];
@@ -900,12 +961,26 @@ __device__ __forceinline__ void tail_interaction(const BatchDev &B, const RayQue
   sig_add(sig, lb.ev);
   const bool cache_here = holo && J.use_cache && !lb.delta && (b - bP + 1) >= J.cache_depth;
   const bool nee_here = nee && !lb.delta && !cache_here;
+  bool query = false;   // an occlusion query goes with the ray
+  if (EXT) Sh.tmax[threadIdx.x] = 0.f;
   if (EXT && nee_here) {
     U4 wn = philox(st.ka, st.kb, (b << 8) | 1u, stream, (uint32_t)J.seed, (uint32_t)(J.seed >> 32));
-    L += beta * next_event(S, M, m, comp, x, d_in, ng, gid, wn, *St, sig);
+    const LightSample s = next_event(S, M, m, comp, x, d_in, ng, wn);
+    query = s.tmax > 0.f;
+    if (query) {
+      const uint32_t t = threadIdx.x;
+      Sh.dx[t] = s.d.x; Sh.dy[t] = s.d.y; Sh.dz[t] = s.d.z; Sh.tmax[t] = s.tmax;
+      Sh.beta[t] = beta; Sh.c[t] = s.c; Sh.sig[t] = s.sig;
+    } else {
+      sig_add(sig, s.sig);
+    }
   }
-  if (lb.w == 0.f) { finish(B, U, J, st, K_ABSORBED, b, L, sig, holo); return; }
+  if (lb.w == 0.f && !(EXT && query)) { finish(B, U, J, st, K_ABSORBED, b, L, sig, holo); return; }
   st.pdf = (EXT && nee_here) ? eval_lobe<EXT>(m, comp, d_in, ng, lb.d).pdf : 0.f;
+  if (EXT && lb.w == 0.f) {   // ends in the next pass, when its query is answered
+    st.pdf = -1.f;
+    atomicSub(&B.counters[2], 1u);   // (no ray)
+  }
   beta *= lb.w;
   if (cache_here) {
     uint32_t res = S.cache_res, nb = S.cache_bins * S.cache_bins;
@@ -944,7 +1019,7 @@ template <bool EXT>
 __device__ __forceinline__ void shade_one(const BatchDev &B, int q, uint32_t i, RayState &st, StageLds &G,
                                           const UnitDev &U, const JobDev &J, const SceneDev &S,
                                           const MaterialDev *M, float t, int32_t hp, const HitRec &H,
-                                          const Stack *St, Emit &e) {
+                                          ShadowLds &Sh, Emit &e) {
   const RayQueue &Q = B.Q[q];
   uint32_t meta = st.meta;
   uint32_t stage = meta & 1u, b = (meta >> 1) & 63u, bP = (meta >> 7) & 63u;
@@ -1021,11 +1096,12 @@ __device__ __forceinline__ void shade_one(const BatchDev &B, int q, uint32_t i, 
     sig_add(sig, EV_IMAGE_POINT);
     image_point(B, Q, U, J, st, ell, b);
     tail_interaction<EXT>(B, Q, G, U, J, S, M, st, to_f(x), to_f(d), H, b, b, comp, stream, 1.0f, 0.0f, sig, t,
-                          St, e);
+                          Sh, e);
     return;
   }
   // incoherent tail (or cache path)
   float beta = st.beta, L = st.L;
+  if (EXT && st.pdf < 0.f) { finish(B, U, J, st, K_ABSORBED, b, L, sig, holo); return; }
   float4 r0 = Q.ray[2 * i], r1 = Q.ray[2 * i + 1];
   if (gid < 0) {
     L += beta * S.env[comp];
@@ -1037,23 +1113,26 @@ __device__ __forceinline__ void shade_one(const BatchDev &B, int q, uint32_t i, 
   sig_add(sig, (uint32_t)gid + 1u);
   F3 d_in = f3(r1.x, r1.y, r1.z);
   F3 x = f3(r0.x, r0.y, r0.z) + t * d_in;
-  tail_interaction<EXT>(B, Q, G, U, J, S, M, st, x, d_in, H, b, bP, comp, stream, beta, L, sig, t, St, e);
+  tail_interaction<EXT>(B, Q, G, U, J, S, M, st, x, d_in, H, b, bP, comp, stream, beta, L, sig, t, Sh, e);
 }
 
 // EXT: batches that use next-event estimation or principled materials (the
-// base kernel leaves both out to keep its registers). Shading then may run
-// occlusion queries: the traversal stack takes kStackLds entries per lane in
-// LDS and the lane's column of the traversal spill, so the grid is capped at
-// the spill's columns and walks the queue with a plain grid stride.
+// base kernel leaves both out to keep its registers). A light sample's
+// occlusion query goes with the path's next ray to the traversal, which answers
+// it with seven waves per SIMD, the top nodes in LDS and its lanes refilled; run
+// here, at the two waves that a traversal inside this kernel left, it took most
+// of a 300x200 hologram with direct light: 6.37 ms, now 3.77 (3.93 with this
+// kernel still at two waves).
 // UNI: a batch of one job whose scene has at most kLdsMats materials and
 // which has at most kLdsUnits units; its job, scene, material and unit
 // descriptors are read from LDS.
 template <bool FIRST, bool EXT, bool UNI>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(EXT ? 2 : 3))) k_shade(BatchDev B, int q, uint32_t pass) {
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) k_shade(BatchDev B, int q, uint32_t pass) {
   // FIRST: queue 0 as ray generation wrote it (dense); else a compacted
   // queue, read through its index list
   __shared__ StageLds G;
-  __shared__ int32_t nee_stack[EXT ? (1 + kStackLds) * kBlock : 1];
+  __shared__ char shadow_lds[EXT ? sizeof(ShadowLds) : 16] __attribute__((aligned(16)));
+  ShadowLds &Sh = *(ShadowLds *)shadow_lds;   // (not reached in the base kernel)
   __shared__ JobDev lds_job[1];
   __shared__ SceneDev lds_scene[1];
   __shared__ MaterialDev lds_mats[UNI ? kLdsMats : 1];
@@ -1067,16 +1146,13 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(EXT
   // touch the same slot windows, so each XCD (the hardware deals workgroups
   // to the 8 XCDs in turn; the grid is a multiple of 8) takes one contiguous
   // eighth of the chunks, which its workgroups walk with a stride of their
-  // number; the extended kernel walks all chunks with a plain grid stride.
+  // number.
   const uint32_t nb8 = ((n + blockDim.x - 1) / blockDim.x + 7u) & ~7u;
   const uint32_t b = blockIdx.x, per = nb8 / 8u;
-  const uint32_t c0 = EXT ? b : (b % 8u) * per + b / 8u;
-  const uint32_t cstep = EXT ? gridDim.x : gridDim.x / 8u;
-  const uint32_t cend = EXT ? nb8 : (b % 8u + 1u) * per;
+  const uint32_t c0 = (b % 8u) * per + b / 8u;
+  const uint32_t cstep = gridDim.x / 8u;
+  const uint32_t cend = (b % 8u + 1u) * per;
   if (c0 >= cend || c0 * blockDim.x >= n) return;  // no entries for this workgroup
-  const Stack St{(LdsI32)(nee_stack + (EXT ? kBlock + threadIdx.x : 0u)), kBlock,
-                 (GlbI32)(B.stack_spill + blockIdx.x * blockDim.x + threadIdx.x), B.spill_threads, nullptr, 0u};
-  if (EXT) stack_floor(St);
   if (UNI) {
     const uint32_t t = threadIdx.x;
     const uint32_t *jsrc = (const uint32_t *)B.job_uniform, *ssrc = (const uint32_t *)B.scene_uniform;
@@ -1117,7 +1193,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(EXT
       e.sig = (J.debug & 5u) != 0;
       if (FIRST) load_first(Qc, i, st, U, J);
       else load_state<EXT>(Qc, i, st, e.sig, U, J, pass);
-      shade_one<EXT>(B, q, i, st, G, U, J, S, M, t, hp, H, &St, e);
+      shade_one<EXT>(B, q, i, st, G, U, J, S, M, t, hp, H, Sh, e);
     }
     // compaction within the chunk: the continuing rays of chunk c take
     // entries [256 c, 256 c + count) of the next queue in lane order (wave
@@ -1138,7 +1214,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(EXT
     }
     __syncthreads();
     const uint32_t before = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-    if (e.on) stage_store<EXT>(G, B.Q[qo], chunk_base + wave_base[wv] + before, e.sig);
+    if (e.on) stage_store<EXT>(G, Sh, B.Q[qo], chunk_base + wave_base[wv] + before, e.sig);
   }
 }
 
@@ -1731,11 +1807,14 @@ uint32_t trace_grid(uint32_t n_paths) {
 
 uint32_t trace_block() { return kBlock; }
 
-hipError_t launch_trace(const BatchDev &B, int q, bool dense, bool count, hipStream_t st) {
+hipError_t launch_trace(const BatchDev &B, int q, bool dense, bool count, bool nee, hipStream_t st) {
   uint32_t g = trace_grid(B.n_paths);
   if ((uint64_t)g * kBlock > B.spill_threads) return hipErrorInvalidValue;
-  auto k = count ? (B.scene_uniform ? k_trace<true, true> : k_trace<true, false>)
-                 : (B.scene_uniform ? k_trace<false, true> : k_trace<false, false>);
+  const bool one = B.scene_uniform != nullptr;
+  auto k = count ? (one ? (nee ? k_trace<true, true, true> : k_trace<true, true, false>)
+                        : (nee ? k_trace<true, false, true> : k_trace<true, false, false>))
+                 : (one ? (nee ? k_trace<false, true, true> : k_trace<false, true, false>)
+                        : (nee ? k_trace<false, false, true> : k_trace<false, false, false>));
   hipLaunchKernelGGL(k, dim3(g), dim3(kBlock), 0, st, B, q, dense ? 1 : 0);
   return hipGetLastError();
 }
@@ -1756,12 +1835,11 @@ uint32_t shade_lds_units() { return kLdsUnits; }
 hipError_t launch_shade(const BatchDev &B, int q, uint32_t pass, bool ext, bool uni, hipStream_t st) {
   const bool first = pass == 0;
   const uint32_t g = min(round8(grid_for(B.n_paths)), kShadeGridMax);
-  const uint32_t gn = ext ? min(g, B.spill_threads / (uint32_t)kBlock) : g;  // one spill column per lane
   auto k = ext ? (first ? (uni ? k_shade<true, true, true> : k_shade<true, true, false>)
                         : (uni ? k_shade<false, true, true> : k_shade<false, true, false>))
                : (first ? (uni ? k_shade<true, false, true> : k_shade<true, false, false>)
                         : (uni ? k_shade<false, false, true> : k_shade<false, false, false>));
-  hipLaunchKernelGGL(k, dim3(gn), dim3(kBlock), 0, st, B, q, pass);
+  hipLaunchKernelGGL(k, dim3(g), dim3(kBlock), 0, st, B, q, pass);
   return hipGetLastError();
 }
 

@@ -15,7 +15,7 @@ hipError_t launch_raygen(const BatchDev &B, bool uni, hipStream_t st);
 // Fails (hipErrorInvalidValue) if the batch's stack spill is too small.
 // dense: queue q is the first queue (ray generation order), else it is read
 // through its index list.
-hipError_t launch_trace(const BatchDev &B, int q, bool dense, bool count, hipStream_t st);
+hipError_t launch_trace(const BatchDev &B, int q, bool dense, bool count, bool nee, hipStream_t st);
 // After the shading pass over queue q: prefix sums of the per-chunk counts
 // of queue q^1, its ray count and its index list.
 hipError_t launch_compact(const BatchDev &B, int q, hipStream_t st);

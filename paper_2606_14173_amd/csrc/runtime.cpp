@@ -528,6 +528,7 @@ hpt_status launch_batch(hpt_ctx *C, int si, int prev) {
   uint32_t slot = 0, acc = 0, max_b = 0;
   L.has_holo = L.has_cache = L.has_f64 = L.has_f32 = L.has_ext = false;
   L.pts_max_pn = 0;
+  bool nee = false;
   for (size_t k = 0; k < P.size(); ++k) {
     const Unit &u = P[k].job->units[P[k].unit];
     UnitDev &d = L.h_units[k];
@@ -538,6 +539,7 @@ hpt_status launch_batch(hpt_ctx *C, int si, int prev) {
     acc += u.kind == UNIT_HOLO ? u.p_n * frame_group(J.T) : u.p_n;
     max_b = std::max(max_b, J.max_bounces);
     if (P[k].job->ext) L.has_ext = true;
+    if (J.nee && P[k].job->scene->host.n_lights) nee = true;
     if (u.kind == UNIT_HOLO) {
       L.has_holo = true;
       if (J.phase_mode == HPT_PHASE_FP64) L.has_f64 = true; else L.has_f32 = true;
@@ -578,7 +580,7 @@ hpt_status launch_batch(hpt_ctx *C, int si, int prev) {
                    B.n_units <= shade_lds_units();
   for (uint32_t it = 0; it <= max_b; ++it) {
     int q = (int)(it & 1u);
-    timed_launch(L, HPT_K_TRACE, S, e, [&] { return launch_trace(B, q, it == 0 || B.dense, profile >= 2, S); });
+    timed_launch(L, HPT_K_TRACE, S, e, [&] { return launch_trace(B, q, it == 0 || B.dense, profile >= 2, it > 0 && nee, S); });
     timed_launch(L, HPT_K_SHADE, S, e, [&] { return launch_shade(B, q, it, L.has_ext, uni, S); });
     // the last pass ends every path (interaction max_b + 1 exceeds the
     // budget), so only the earlier ones leave rays to order
