@@ -18,10 +18,10 @@ __device__ __forceinline__ U4 philox(uint32_t c0, uint32_t c1, uint32_t c2, uint
                                      uint32_t k0, uint32_t k1) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
-    uint32_t lo0 = 0xD2511F53u * c0, hi0 = __umulhi(0xD2511F53u, c0);
-    uint32_t lo1 = 0xCD9E8D57u * c2, hi1 = __umulhi(0xCD9E8D57u, c2);
-    uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
-    c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
+    // (one 32 x 32 -> 64 bit multiplication each)
+    const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
+    const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0, n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+    c0 = n0; c1 = (uint32_t)p1; c2 = n2; c3 = (uint32_t)p0;
     k0 += 0x9E3779B9u; k1 += 0xBB67AE85u;
   }
   return {c0, c1, c2, c3};
@@ -30,6 +30,13 @@ __device__ __forceinline__ U4 philox(uint32_t c0, uint32_t c1, uint32_t c2, uint
 // 24-bit uniforms: exact in float and double.
 __device__ __forceinline__ float uf(uint32_t w) { return (float)(w >> 8) * 5.9604644775390625e-08f; }
 __device__ __forceinline__ double ud(uint32_t w) { return (double)(w >> 8) * 5.9604644775390625e-08; }
+
+// n / d and n % d for n < 2^31, m = div_magic(d).
+__device__ __forceinline__ void div_mod(uint32_t n, uint32_t d, uint32_t m, uint32_t &q, uint32_t &r) {
+  q = __umulhi(n, m);
+  r = n - q * d;
+  if (r >= d) { ++q; r -= d; }
+}
 
 // ------------------------------------------------------------------ signature
 __device__ __forceinline__ void sig_add(unsigned long long &h, uint32_t w) {

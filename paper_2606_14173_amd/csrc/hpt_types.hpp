@@ -95,6 +95,12 @@ struct alignas(64) HitRec {
 };
 static_assert(sizeof(HitRec) == 64, "HitRec is one 64-byte record");
 
+// n / d of n < 2^31 by the device's div_mod: a multiplication with
+// div_magic(d) = floor((2^32 - 1) / d) gives the quotient or one less (n / 2^32
+// times 1 + 1 / d, at most 1, is lost before rounding down), which the remainder
+// tells. Six instructions, where the compiler's division takes twenty-five.
+inline uint32_t div_magic(uint32_t d) { return d ? 0xFFFFFFFFu / d : 0u; }
+
 // Device view of one resident scene.
 struct SceneDev {
   const float4 *nodes;       // BVH2: 3 x float4 per node (pack_nodes)
@@ -126,8 +132,11 @@ struct JobDev {
   uint32_t crop_x0, crop_y0, crop_w, crop_h;
   uint32_t n_ch;
   uint32_t comp[3];
-  double lambda[3], inv_lambda[3], s_cone[3];
-  float lambda_f[3], inv_lambda_f[3], s_cone_f[3];
+  double inv_lambda[3], s_cone[3];
+  float inv_lambda_f[3], s_cone_f[3];
+  // div_magic of what pixel and texel indices are divided by: 8 crop_w, 8 (crop_h
+  // mod 8), crop_w mod 8, width, grf_w, grf_h
+  uint32_t band_m, last_m, edge_m, width_m, grf_w_m, grf_h_m;
   uint32_t spp, max_bounces, T, phase_mode, random_phase, use_cache, cache_depth, debug;
   uint64_t seed;
   double Tm[12], Ti[12];
@@ -151,7 +160,8 @@ struct JobDev {
 // crop (row-major) x samples [s_lo, s_lo + s_n) of one channel; or cache
 // entries x paths per entry of one colour component.
 struct UnitDev {
-  uint32_t kind, ch;
+  uint16_t kind, ch;
+  uint32_t s_n_m;            // div_magic(s_n)
   uint32_t p_lo, p_n, s_lo, s_n;
   uint32_t slot_base, acc_base;
   const JobDev *job;

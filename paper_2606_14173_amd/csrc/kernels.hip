@@ -57,20 +57,20 @@ __device__ __forceinline__ F3 hit_normal32(const SceneDev &S, const HitRec &H, F
 // one small tile.
 __device__ __forceinline__ void crop_xy(const JobDev &J, uint32_t p, uint32_t &cx, uint32_t &cy) {
   uint32_t w = J.crop_w, h = J.crop_h;
-  uint32_t band = p / (8u * w);                 // 8-row band
+  uint32_t band, o;                             // 8-row band, and the place in it
+  div_mod(p, 8u * w, J.band_m, band, o);
   uint32_t rows = min(8u, h - 8u * band);
-  uint32_t o = p - band * 8u * w;
   uint32_t full = (w / 8u) * 8u * rows;         // pixels in the band's full-width tiles
   uint32_t tx, ix, iy;
   if (o < full) {
-    tx = o / (8u * rows);
-    uint32_t in = o - tx * 8u * rows;
+    uint32_t in;
+    if (rows == 8u) { tx = o / 64u; in = o % 64u; }
+    else div_mod(o, 8u * rows, J.last_m, tx, in);
     iy = in / 8u; ix = in - iy * 8u;
     cx = tx * 8u + ix;
   } else {
     uint32_t wp = w - (w / 8u) * 8u;              // width of the last, partial tile
-    uint32_t in = o - full;
-    iy = in / wp; ix = in - iy * wp;
+    div_mod(o - full, wp, J.edge_m, iy, ix);
     cx = (w / 8u) * 8u + ix;
   }
   cy = band * 8u + iy;
@@ -80,8 +80,7 @@ __device__ __forceinline__ void crop_xy(const JobDev &J, uint32_t p, uint32_t &c
 __device__ __forceinline__ void slot_decode(const UnitDev &U, uint32_t slot, uint32_t &p_local,
                                             uint32_t &s_local) {
   uint32_t l = slot - U.slot_base;
-  p_local = l / U.s_n;
-  s_local = l - p_local * U.s_n;
+  div_mod(l, U.s_n, U.s_n_m, p_local, s_local);
 }
 
 // Philox key words of path slot `slot` of unit U: (global pixel index,
@@ -374,7 +373,9 @@ __device__ __forceinline__ void load_first(const RayQueue &Q, uint32_t i, RaySta
     r.meta = STAGE_PREFIX;
     double al, be;
     cone_cosines(U, J, r.ka, r.kb, al, be);
-    primary_ray(J, r.ka % J.width, r.ka / J.width, al, be, r.o, r.d);
+    uint32_t px, py;
+    div_mod(r.ka, J.width, J.width_m, py, px);
+    primary_ray(J, px, py, al, be, r.o, r.d);
     r.ell = 0.0;
   } else {
     r.meta = STAGE_TAIL;
@@ -786,6 +787,19 @@ __device__ __forceinline__ void finish(const BatchDev &B, const UnitDev &U, cons
   if (J.debug & 1u) write_rec_tail(J, U, B, slot, kind, b, A, amp, sig);
 }
 
+// The texel that whole coordinate f falls in on a periodic grid of n texels, m =
+// div_magic(n); -1 - k is as far from the end as k is from the start.
+__device__ __forceinline__ uint32_t wrap(double f, uint32_t n, uint32_t m) {
+  if (fabs(f) < 2147483648.0) {
+    const int32_t i = (int32_t)f;
+    uint32_t q, r;
+    div_mod((uint32_t)(i ^ (i >> 31)), n, m, q, r);
+    return i < 0 ? n - 1u - r : r;
+  }
+  const int64_t i = (int64_t)f % (int64_t)n;
+  return (uint32_t)(i < 0 ? i + n : i);
+}
+
 // s6-s7: image point of a path whose coherent prefix ended at a non-delta
 // hit after optical path length ell: P' = O + ell v, Q = T P',
 // r = |Q - x_p|, weight W = r / p(v) with p(v) = v_z / (pi s^2); phase
@@ -794,7 +808,8 @@ __device__ __forceinline__ void image_point(const BatchDev &B, const RayQueue &Q
                                             const JobDev &J, RayState &st, double ell, uint32_t bP) {
   const uint32_t slot = st.slot;
   uint32_t gpix = st.ka;
-  uint32_t px = gpix % J.width, py = gpix / J.width;
+  uint32_t px, py;
+  div_mod(gpix, J.width, J.width_m, py, px);
   double al, be;
   cone_cosines(U, J, st.ka, st.kb, al, be);
   double s = J.s_cone[U.ch];
@@ -859,11 +874,8 @@ __device__ __forceinline__ void image_point(const BatchDev &B, const RayQueue &Q
     v = Q.y / (float)J.pitch + 0.5f * (float)J.height - 0.5f;
   }
   double fu = floor(u), fv = floor(v);
-  int64_t i0 = (int64_t)fu % (int64_t)J.grf_w, j0 = (int64_t)fv % (int64_t)J.grf_h;
-  if (i0 < 0) i0 += J.grf_w;
-  if (j0 < 0) j0 += J.grf_h;
   PathRes &res = B.res[slot];
-  res.tex = (uint32_t)i0 | ((uint32_t)j0 << 16);
+  res.tex = wrap(fu, J.grf_w, J.grf_w_m) | (wrap(fv, J.grf_h, J.grf_h_m) << 16);
   res.fx = u - fu;
   res.fy = v - fv;
   // unit phasor exp(i k r) of the path (the same for all T frames), in the
@@ -1525,10 +1537,8 @@ __device__ __forceinline__ float2 grf_unit(const JobDev &J, uint32_t t, double q
   const double u = qx / J.pitch + 0.5 * (double)J.width - 0.5;
   const double v = qy / J.pitch + 0.5 * (double)J.height - 0.5;
   const double fu = floor(u), fv = floor(v);
-  int64_t i0 = (int64_t)fu % (int64_t)J.grf_w, j0 = (int64_t)fv % (int64_t)J.grf_h;
-  if (i0 < 0) i0 += J.grf_w;
-  if (j0 < 0) j0 += J.grf_h;
-  const uint32_t i1 = i0 + 1 == J.grf_w ? 0 : (uint32_t)i0 + 1, j1 = j0 + 1 == J.grf_h ? 0 : (uint32_t)j0 + 1;
+  const uint32_t i0 = wrap(fu, J.grf_w, J.grf_w_m), j0 = wrap(fv, J.grf_h, J.grf_h_m);
+  const uint32_t i1 = i0 + 1 == J.grf_w ? 0 : i0 + 1, j1 = j0 + 1 == J.grf_h ? 0 : j0 + 1;
   const auto G2 = glb(J.grf) + t;
   const size_t gw = J.grf_w, T = J.T;
   const float2 qa = G2[((size_t)j0 * gw + i0) * T], qb = G2[((size_t)j0 * gw + i1) * T],

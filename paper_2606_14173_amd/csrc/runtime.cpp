@@ -532,7 +532,7 @@ hpt_status launch_batch(hpt_ctx *C, int si, int prev) {
   for (size_t k = 0; k < P.size(); ++k) {
     const Unit &u = P[k].job->units[P[k].unit];
     UnitDev &d = L.h_units[k];
-    d.kind = u.kind; d.ch = u.ch; d.p_lo = u.p_lo; d.p_n = u.p_n; d.s_lo = u.s_lo; d.s_n = u.s_n;
+    d.kind = (uint16_t)u.kind; d.ch = (uint16_t)u.ch; d.s_n_m = div_magic(u.s_n); d.p_lo = u.p_lo; d.p_n = u.p_n; d.s_lo = u.s_lo; d.s_n = u.s_n;
     d.slot_base = slot; d.acc_base = acc; d.job = P[k].job->dev; d.scene = P[k].job->scene->dev;
     const JobDev &J = P[k].job->host;
     slot += u.p_n * u.s_n;
@@ -1331,10 +1331,8 @@ hpt_status hpt_trace_submit(hpt_ctx *C, uint64_t scene, const hpt_job_desc *d, v
   jd.n_ch = d->n_ch;
   for (uint32_t c = 0; c < d->n_ch; ++c) {
     jd.comp[c] = d->comp[c];
-    jd.lambda[c] = d->lambda[c];
     jd.inv_lambda[c] = 1.0 / d->lambda[c];
     jd.s_cone[c] = d->lambda[c] / (2.0 * d->pitch);
-    jd.lambda_f[c] = (float)jd.lambda[c];
     jd.inv_lambda_f[c] = (float)jd.inv_lambda[c];
     jd.s_cone_f[c] = (float)jd.s_cone[c];
   }
@@ -1351,6 +1349,8 @@ hpt_status hpt_trace_submit(hpt_ctx *C, uint64_t scene, const hpt_job_desc *d, v
   static const double I[12] = {1, 0, 0, 0, 0, 1, 0, 0, 0, 0, 1, 0};
   jd.identity_T = std::memcmp(I, d->holo_from_world, sizeof(I)) == 0 ? 1 : 0;
   jd.grf_w = d->grf_w; jd.grf_h = d->grf_h;
+  jd.band_m = div_magic(8 * cw); jd.last_m = div_magic(8 * (ch % 8)); jd.edge_m = div_magic(cw % 8);
+  jd.width_m = div_magic(d->width); jd.grf_w_m = div_magic(d->grf_w); jd.grf_h_m = div_magic(d->grf_h);
   jd.spp_lo = sb; jd.n_s = se - sb;
   jd.scene = S->dev;
   J->field_elems = (size_t)d->n_ch * d->T * cw * ch;
