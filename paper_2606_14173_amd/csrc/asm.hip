@@ -20,11 +20,22 @@
 // observation plane, and k_ifft_rows_intensity sums |u|^2 over the fields
 // instead of writing them.
 //
-// The line FFTs are in fft.hpp. What bounds the passes, 24 fields of 1920 x
-// 1080 (4096 x 4096 padded): the row passes run at the memory's rate (10.5 us
-// a field each for 52 MB, 4.9 TB/s; 26 us while their twiddles were gathers),
-// the column pass by vector issue in one workgroup per CU (60 us a field, 58 %
-// of its issue slots; 96 us before, and two transposes of 12 us each beside it).
+// The line FFTs are in fft.hpp. Row spectra whose columns are long (Py >= 2048)
+// lie in tiles of eight columns (asm_tiled): a workgroup of two columns then reads
+// neighbouring 64-byte pieces, where in plain order it would use 16 bytes of a
+// line of the cache per row, and the row passes take two rows at once. Two
+// workgroups of two columns run on a CU, one's memory beside the other's
+// arithmetic; one of four in plain order had all its waves wait together.
+// What bounds the passes, 24 fields of 1920 x 1080 (4096 x 4096 padded): the
+// column pass by vector issue and LDS (51 us a field; 60 with one workgroup of
+// four columns, 96 with transposes of 12 us each beside it), the row passes by
+// memory (13 and 11 us a field for 52 MB; 11 and 9 in plain order, 26 while their
+// twiddles were gathers). All together 1.74 ms (1.93 in plain order); phase
+// encoding of 1920 x 1080, whose fields exceed the last-level cache, 80 ms (94).
+// Tiles of 4 and 16 columns 82 and 84 ms. With short columns the plain order is as
+// fast or faster (1080 x 200: 0.19 ms, tiled 0.20), and so are several planes in
+// workgroups of four (focal stack 6.8 ms, of two 8.3: each plane's transfer
+// function is read in 16-byte pieces).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -40,15 +51,16 @@ namespace {
 using namespace fft;
 
 // Forward FFT of row (f, y) of in [nf][h][w], zero-padded to Px -> A [nf][h][Px].
-template <int LG>
-__global__ void __launch_bounds__(Rows<LG>::W) k_fft_rows(const float2 *in, float2 *A, uint32_t w, uint32_t nrows,
-                                                          const float2 *tw) {
+template <int LG, bool TILED>
+__global__ void __launch_bounds__((Rows<LG, TILED>::W))
+    k_fft_rows(const float2 *in, float2 *A, uint32_t w, uint32_t h, uint32_t nrows, const float2 *tw) {
   using L = Line<LG>;
-  __shared__ C2 lds[Rows<LG>::kLdsElems];
-  const uint32_t l = threadIdx.x / L::TPL, t = threadIdx.x % L::TPL;
-  const size_t row = (size_t)blockIdx.x * Rows<LG>::kLines + l;  // f * h + y
+  using Lines = Rows<LG, TILED>;
+  __shared__ C2 lds[Lines::kLdsElems];
+  const uint32_t l = Lines::line(), t = Lines::pos();
+  const uint32_t row = Lines::group() * Lines::kLines + l;  // f * h + y
   const bool ok = row < nrows;
-  const float2 *src = in + row * w;
+  const float2 *src = in + (size_t)row * w;
   C2 v[L::E];
 #pragma unroll
   for (uint32_t q = 0; q < L::E / 2; ++q) {  // w <= Px / 2
@@ -56,11 +68,12 @@ __global__ void __launch_bounds__(Rows<LG>::W) k_fft_rows(const float2 *in, floa
     const float2 g = ok && i < w ? src[i] : make_float2(0.f, 0.f);
     v[q] = c2(g.x, g.y);
   }
-  line_fft<LG, false, true, 1, Rows<LG>::kWave, false>(v, lds + l * L::kLds, TableTwiddles{tw}, t);
+  line_fft<LG, false, true, Lines::kStride, Lines::kWave, false>(v, Lines::lds_of(lds), TableTwiddles{tw}, t);
   if (!ok) return;
-  float2 *dst = A + row * L::N;
+  const uint32_t f = TILED ? row / h : row, y = TILED ? row - f * h : 0u, first = Lines::first_of(t, y, h);
+  float2 *dst = A + (size_t)f * (TILED ? h : 1u) * L::N;
 #pragma unroll
-  for (uint32_t q = 0; q < L::E; ++q) dst[t + q * L::TPL] = make_float2(v[q].x, v[q].y);
+  for (uint32_t q = 0; q < L::E; ++q) Lines::elem(dst, first, h, q) = make_float2(v[q].x, v[q].y);
 }
 
 // Columns of a workgroup: kCols neighbouring columns (c fastest in the
@@ -68,28 +81,16 @@ __global__ void __launch_bounds__(Rows<LG>::W) k_fft_rows(const float2 *in, floa
 // segment of kCols x 8 bytes), TPL threads each. The lines of the cache that
 // neighbouring workgroups share are met in the L2 of the XCD they run on
 // (xcd_group), which costs less than the two transposes that contiguous
-// columns would need. Long columns: four of 4096 points fill the CU's LDS
-// (139 KB) with one workgroup.
-template <int LG>
+// columns would need. Of long columns two (LDS of half a CU), four where several
+// planes' transfer functions are read and the LDS holds them.
+template <int LG, bool PLANES>
 struct Cols {
-  static constexpr uint32_t kCols = LG >= 13 ? 2 : LG >= 10 ? 4 : LG == 9 ? 8 : LG >= 6 ? 16 : 32;
+  static constexpr bool kTwo = LG >= 13 || (LG >= 11 && !PLANES);
+  static constexpr uint32_t kCols = kTwo ? 2 : LG >= 10 ? 4 : LG == 9 ? 8 : LG >= 6 ? 16 : 32;
   static constexpr uint32_t W = kCols * Line<LG>::TPL;
   static constexpr uint32_t kLdsElems = LG > 4 ? kCols * Line<LG>::kLds : 1;
   static constexpr uint32_t kWaves = LG >= 10 ? 4 : 2;
 };
-
-// Element at a byte offset from a uniform base: a scalar base and a 32-bit
-// offset register. (The offset goes through an empty asm so that its
-// extension to 64 bits stays beside the access; hoisted, every access would
-// add two registers' worth of address instead.)
-__device__ __forceinline__ const float2 &at(const float2 *p, uint32_t off) {
-  asm volatile("" : "+v"(off));
-  return *(const float2 *)((const char *)p + off);
-}
-__device__ __forceinline__ float2 &at(float2 *p, uint32_t off) {
-  asm volatile("" : "+v"(off));
-  return *(float2 *)((char *)p + off);
-}
 
 // A loop's index, unknown to the optimiser: it would else keep one 64-bit
 // address per access of the body over the iterations (32 registers) instead
@@ -99,23 +100,17 @@ __device__ __forceinline__ uint32_t opaque(uint32_t i) {
   return i;
 }
 
-// Group of columns of workgroup b of g: each of the 8 XCDs (workgroups are
-// dealt to them in turn) takes one contiguous range.
-__device__ __forceinline__ uint32_t xcd_group(uint32_t b, uint32_t g) {
-  return g % 8u ? b : (b % 8u) * (g / 8u) + b / 8u;
-}
-
 // A group of columns of fields [blockIdx.y * fpw, + fpw): src [nf][h][Px]
 // holds the row spectra. H: transfer functions of np planes, each [Py/2 +
 // 1][Px/2 + 1]. dst [np][nf][h][Px]; may be src when np is 1 (every column
 // is read before it is written).
 template <int LG, bool PLANES>
-__global__ void __launch_bounds__(Cols<LG>::W, Cols<LG>::kWaves) k_fft_columns(const float2 *src, float2 *dst, const float2 *H,
-                                                             uint32_t np, uint32_t nf, uint32_t fpw, uint32_t h,
-                                                             uint32_t px, const float2 *tw) {
+__global__ void __launch_bounds__((Cols<LG, PLANES>::W), (Cols<LG, PLANES>::kWaves))
+    k_fft_columns(const float2 *src, float2 *dst, const float2 *H, uint32_t np, uint32_t nf, uint32_t fpw, uint32_t h,
+                  uint32_t px, uint32_t tile_lg, const float2 *tw) {
   using L = Line<LG>;
-  constexpr uint32_t C = Cols<LG>::kCols, E = L::E;
-  __shared__ C2 lds[Cols<LG>::kLdsElems];
+  constexpr uint32_t C = Cols<LG, PLANES>::kCols, E = L::E;
+  __shared__ C2 lds[Cols<LG, PLANES>::kLdsElems];
   const uint32_t c = threadIdx.x % C, t = threadIdx.x / C;
   // lanes past the last column (px < C) work on column 0 and store nothing
   const uint32_t col = xcd_group(blockIdx.x, gridDim.x) * C + c, kx = col < px ? col : 0u;
@@ -126,8 +121,9 @@ __global__ void __launch_bounds__(Cols<LG>::W, Cols<LG>::kWaves) k_fft_columns(c
   const size_t field = (size_t)h * px;
   // element (row t + q TPL, column kx) of a field: q steps from a uniform
   // base, plus one byte offset (below 2^32: h <= 4096, px <= 8192)
-  const size_t step = (size_t)L::TPL * px;
-  const uint32_t off = (t * px + kx) * 8;
+  // (tiles of 2^tile_lg columns)
+  const uint32_t step = L::TPL << tile_lg;
+  const uint32_t off = ((((kx >> tile_lg) * h + t) << tile_lg) + (kx & ((1u << tile_lg) - 1u))) * 8;
   auto load_h = [&](C2 (&Hr)[E], const float2 *T) {
     // frequency row i = t + q TPL: |f_y| is i steps, from q = E/2 on N - i
     const uint32_t up = (t * hw + hx) * 8, down = ((L::TPL - 1 - t) * hw + hx) * 8;
@@ -144,7 +140,8 @@ __global__ void __launch_bounds__(Cols<LG>::W, Cols<LG>::kWaves) k_fft_columns(c
       if (t + q * L::TPL < h_store) at(out + q * step, off) = make_float2(v[q].x, v[q].y);
     }
   };
-  typename std::conditional<C % 4 == 0, QuadTwiddles<LG>, TableTwiddles>::type T;
+  using Two = typename std::conditional<C == 2 && (LG <= 12 || PLANES), PairTwiddles<LG>, TableTwiddles>::type;
+  typename std::conditional<C % 4 == 0, QuadTwiddles<LG>, Two>::type T;
   T.load(tw, t);
   C2 Hr[E];
   if constexpr (!PLANES) load_h(Hr, H);
@@ -192,23 +189,25 @@ __global__ void __launch_bounds__(Cols<LG>::W, Cols<LG>::kWaves) k_fft_columns(c
 }
 
 // Inverse FFT of row (f, y) of A [nf][h][Px]; keep [0, w), scale -> out [nf][h][w].
-template <int LG>
-__global__ void __launch_bounds__(Rows<LG>::W) k_ifft_rows(const float2 *A, float2 *out, uint32_t w, uint32_t nrows,
-                                                           float scale, const float2 *tw) {
+template <int LG, bool TILED>
+__global__ void __launch_bounds__((Rows<LG, TILED>::W))
+    k_ifft_rows(const float2 *A, float2 *out, uint32_t w, uint32_t h, uint32_t nrows, float scale, const float2 *tw) {
   using L = Line<LG>;
-  __shared__ C2 lds[Rows<LG>::kLdsElems];
-  const uint32_t l = threadIdx.x / L::TPL, t = threadIdx.x % L::TPL;
-  const size_t row = (size_t)blockIdx.x * Rows<LG>::kLines + l;
+  using Lines = Rows<LG, TILED>;
+  __shared__ C2 lds[Lines::kLdsElems];
+  const uint32_t l = Lines::line(), t = Lines::pos();
+  const uint32_t row = Lines::group() * Lines::kLines + l;
   const bool ok = row < nrows;
-  const float2 *src = A + row * L::N;
+  const uint32_t f = TILED ? row / h : row, y = TILED ? row - f * h : 0u, first = Lines::first_of(t, y, h);
+  const float2 *src = A + (size_t)f * (TILED ? h : 1u) * L::N;
   C2 v[L::E];
 #pragma unroll
   for (uint32_t q = 0; q < L::E; ++q) {
-    const float2 g = ok ? src[t + q * L::TPL] : make_float2(0.f, 0.f);
+    const float2 g = ok ? Lines::elem(src, first, h, q) : make_float2(0.f, 0.f);
     v[q] = c2(g.x, g.y);
   }
-  line_fft<LG, true, false, 1, Rows<LG>::kWave, false>(v, lds + l * L::kLds, TableTwiddles{tw}, t);
-  float2 *dst = out + row * w;
+  line_fft<LG, true, false, Lines::kStride, Lines::kWave, false>(v, Lines::lds_of(lds), TableTwiddles{tw}, t);
+  float2 *dst = out + (size_t)row * w;
 #pragma unroll
   for (uint32_t q = 0; q < L::E / 2; ++q) {
     const uint32_t i = t + q * L::TPL;
@@ -220,17 +219,19 @@ __global__ void __launch_bounds__(Rows<LG>::W) k_ifft_rows(const float2 *A, floa
 // of row (f, y) of A [np][nf][h][Px] for every f < nf, scaled by 1/(Px Py),
 // |.|^2 of the first w values summed over f, times `weight`; written into (or
 // added to) I [np][h][w].
-template <int LG>
-__global__ void __launch_bounds__(Rows<LG>::W) k_ifft_rows_intensity(const float2 *A, float *I, uint32_t nf,
+template <int LG, bool TILED>
+__global__ void __launch_bounds__((Rows<LG, TILED>::W)) k_ifft_rows_intensity(const float2 *A, float *I, uint32_t nf,
                                                                      uint32_t w, uint32_t h, float scale,
                                                                      float weight, uint32_t accumulate,
                                                                      const float2 *tw) {
   using L = Line<LG>;
-  __shared__ C2 lds[Rows<LG>::kLdsElems];
-  const uint32_t l = threadIdx.x / L::TPL, t = threadIdx.x % L::TPL;
-  const uint32_t y = blockIdx.x * Rows<LG>::kLines + l;
+  using Lines = Rows<LG, TILED>;
+  __shared__ C2 lds[Lines::kLdsElems];
+  const uint32_t l = Lines::line(), t = Lines::pos();
+  const uint32_t y = Lines::group() * Lines::kLines + l;
   const bool ok = y < h;
-  const float2 *Ap = A + (size_t)blockIdx.y * nf * h * L::N + (size_t)y * L::N;
+  const uint32_t first = Lines::first_of(t, y, h);
+  const float2 *Ap = A + (size_t)blockIdx.y * nf * h * L::N;
   float acc[L::E / 2];
 #pragma unroll
   for (uint32_t q = 0; q < L::E / 2; ++q) acc[q] = 0.f;
@@ -239,10 +240,10 @@ __global__ void __launch_bounds__(Rows<LG>::W) k_ifft_rows_intensity(const float
     C2 v[L::E];
 #pragma unroll
     for (uint32_t q = 0; q < L::E; ++q) {
-      const float2 g = ok ? src[t + q * L::TPL] : make_float2(0.f, 0.f);
+      const float2 g = ok ? Lines::elem(src, first, h, q) : make_float2(0.f, 0.f);
       v[q] = c2(g.x, g.y);
     }
-    line_fft<LG, true, false, 1, Rows<LG>::kWave, false>(v, lds + l * L::kLds, TableTwiddles{tw}, t);
+    line_fft<LG, true, false, Lines::kStride, Lines::kWave, false>(v, Lines::lds_of(lds), TableTwiddles{tw}, t);
 #pragma unroll
     for (uint32_t q = 0; q < L::E / 2; ++q) {
       const float re = v[q].x * scale, im = v[q].y * scale;
@@ -351,18 +352,24 @@ size_t asm_transfer_elems(uint32_t w, uint32_t h) {
   return (size_t)(asm_padded(w) / 2 + 1) * (asm_padded(h) / 2 + 1);
 }
 
+// Whether row spectra are tiled: see the head of this file.
+bool asm_tiled(uint32_t w, uint32_t h) { return asm_padded(h) >= 2048 && asm_padded(w) >= 1u << kTiledLg; }
+
 hipError_t launch_asm_transfer(float2 *T, uint32_t w, uint32_t h, const AsmParams &P, hipStream_t st) {
   const uint32_t nx = asm_padded(w) / 2 + 1, ny = asm_padded(h) / 2 + 1;
   hipLaunchKernelGGL(k_transfer, dim3((nx * ny + 255) / 256), dim3(256), 0, st, T, nx, ny, P);
   return hipGetLastError();
 }
 
-hipError_t launch_asm_rows(const float2 *in, float2 *A, const float2 *tw, uint32_t nrows, uint32_t w, hipStream_t st) {
-  const uint32_t px = asm_padded(w);
-  const bool known = with_length(log2u(px), [&](auto lg) {
+hipError_t launch_asm_rows(const float2 *in, float2 *A, const float2 *tw, uint32_t nf, uint32_t w, uint32_t h,
+                           hipStream_t st) {
+  const uint32_t px = asm_padded(w), nrows = nf * h;
+  const bool known = with_rows(log2u(px), asm_tiled(w, h), [&](auto lg, auto tiled) {
     constexpr int LG = decltype(lg)::value;
-    constexpr uint32_t n = Rows<LG>::kLines;
-    hipLaunchKernelGGL((k_fft_rows<LG>), dim3((nrows + n - 1) / n), dim3(Rows<LG>::W), 0, st, in, A, w, nrows, tw + 2 * px);
+    constexpr bool TILED = decltype(tiled)::value;
+    constexpr uint32_t n = Rows<LG, TILED>::kLines, W = Rows<LG, TILED>::W;
+    hipLaunchKernelGGL((k_fft_rows<LG, TILED>), dim3((nrows + n - 1) / n), dim3(W), 0, st, in, A, w,
+                       h, nrows, tw + 2 * px);
   });
   return known ? hipGetLastError() : hipErrorInvalidValue;
 }
@@ -372,13 +379,13 @@ hipError_t launch_asm_columns(const float2 *src, float2 *dst, const float2 *H, u
   const uint32_t px = asm_padded(w), py = asm_padded(h);
   const bool known = with_length(log2u(py), [&](auto lg) {
     constexpr int LG = decltype(lg)::value;
-    const uint32_t groups = (px + Cols<LG>::kCols - 1) / Cols<LG>::kCols;
-    const uint32_t fpw = fields_per_group(groups, nf);
-    const dim3 grid(groups, (nf + fpw - 1) / fpw), block(Cols<LG>::W);
-    if (np == 1)
-      hipLaunchKernelGGL((k_fft_columns<LG, false>), grid, block, 0, st, src, dst, H, 1u, nf, fpw, h, px, tw + 2 * py);
-    else
-      hipLaunchKernelGGL((k_fft_columns<LG, true>), grid, block, 0, st, src, dst, H, np, nf, fpw, h, px, tw + 2 * py);
+    auto launch = [&](auto kernel, uint32_t cols, uint32_t threads) {
+      const uint32_t groups = (px + cols - 1) / cols, fpw = fields_per_group(groups, nf);
+      hipLaunchKernelGGL(kernel, dim3(groups, (nf + fpw - 1) / fpw), dim3(threads), 0, st, src, dst, H, np, nf, fpw, h, px,
+                         log2u(asm_tiled(w, h) ? kTile : px), tw + 2 * py);
+    };
+    if (np == 1) launch(k_fft_columns<LG, false>, Cols<LG, false>::kCols, Cols<LG, false>::W);
+    else launch(k_fft_columns<LG, true>, Cols<LG, true>::kCols, Cols<LG, true>::W);
   });
   return known ? hipGetLastError() : hipErrorInvalidValue;
 }
@@ -387,13 +394,14 @@ hipError_t launch_asm(const float2 *in, float2 *out, float2 *A, const float2 *H,
                       uint32_t w, uint32_t h, hipStream_t st) {
   if (nf == 0 || w == 0 || h == 0) return hipErrorInvalidValue;
   const uint32_t px = asm_padded(w), py = asm_padded(h), nrows = nf * h;
-  hipError_t e = launch_asm_rows(in, A, tw, nrows, w, st);
+  hipError_t e = launch_asm_rows(in, A, tw, nf, w, h, st);
   if (e == hipSuccess) e = launch_asm_columns(A, A, H, 1, tw, nf, w, h, st);
   if (e != hipSuccess) return e;
-  const bool known = with_length(log2u(px), [&](auto lg) {
+  const bool known = with_rows(log2u(px), asm_tiled(w, h), [&](auto lg, auto tiled) {
     constexpr int LG = decltype(lg)::value;
-    constexpr uint32_t n = Rows<LG>::kLines;
-    hipLaunchKernelGGL((k_ifft_rows<LG>), dim3((nrows + n - 1) / n), dim3(Rows<LG>::W), 0, st, A, out, w, nrows,
+    constexpr bool TILED = decltype(tiled)::value;
+    constexpr uint32_t n = Rows<LG, TILED>::kLines, W = Rows<LG, TILED>::W;
+    hipLaunchKernelGGL((k_ifft_rows<LG, TILED>), dim3((nrows + n - 1) / n), dim3(W), 0, st, A, out, w, h, nrows,
                        1.0f / ((float)px * (float)py), tw + 2 * px);
   });
   return known ? hipGetLastError() : hipErrorInvalidValue;
@@ -402,10 +410,11 @@ hipError_t launch_asm(const float2 *in, float2 *out, float2 *A, const float2 *H,
 hipError_t launch_asm_intensity(const float2 *A, const float2 *tw, uint32_t np, uint32_t nf, uint32_t w, uint32_t h,
                                 float *I, float weight, bool accumulate, hipStream_t st) {
   const uint32_t px = asm_padded(w), py = asm_padded(h);
-  const bool known = with_length(log2u(px), [&](auto lg) {
+  const bool known = with_rows(log2u(px), asm_tiled(w, h), [&](auto lg, auto tiled) {
     constexpr int LG = decltype(lg)::value;
-    constexpr uint32_t n = Rows<LG>::kLines;
-    hipLaunchKernelGGL((k_ifft_rows_intensity<LG>), dim3((h + n - 1) / n, np), dim3(Rows<LG>::W), 0, st, A, I, nf, w, h,
+    constexpr bool TILED = decltype(tiled)::value;
+    constexpr uint32_t n = Rows<LG, TILED>::kLines, W = Rows<LG, TILED>::W;
+    hipLaunchKernelGGL((k_ifft_rows_intensity<LG, TILED>), dim3((h + n - 1) / n, np), dim3(W), 0, st, A, I, nf, w, h,
                        1.0f / ((float)px * (float)py), weight, accumulate ? 1u : 0u, tw + 2 * px);
   });
   return known ? hipGetLastError() : hipErrorInvalidValue;

@@ -38,6 +38,8 @@ hipError_t asm_device(int device, AsmDevice *out);
 // Transfer function of P for fields of w x h, tabulated over a quarter of the
 // frequency plane (asm_transfer_elems complex64: never more than h Px + Px +
 // Py).
+// Whether the row spectra of w x h fields lie in tiles (fft.hpp).
+bool asm_tiled(uint32_t w, uint32_t h);
 size_t asm_transfer_elems(uint32_t w, uint32_t h);
 hipError_t launch_asm_transfer(float2 *T, uint32_t w, uint32_t h, const AsmParams &P, hipStream_t st);
 
@@ -46,8 +48,10 @@ hipError_t launch_asm_transfer(float2 *T, uint32_t w, uint32_t h, const AsmParam
 hipError_t launch_asm(const float2 *in, float2 *out, float2 *A, const float2 *H, const float2 *tw, uint32_t nf,
                       uint32_t w, uint32_t h, hipStream_t st);
 
-// The passes by themselves. Row spectra of nrows rows [nrows][w] -> A [nrows][Px].
-hipError_t launch_asm_rows(const float2 *in, float2 *A, const float2 *tw, uint32_t nrows, uint32_t w, hipStream_t st);
+// The passes by themselves. Row spectra of nf fields [nf][h][w] -> A [nf][h][Px],
+// in tiles if asm_tiled, as all row spectra are.
+hipError_t launch_asm_rows(const float2 *in, float2 *A, const float2 *tw, uint32_t nf, uint32_t w, uint32_t h,
+                           hipStream_t st);
 // Column passes of nf fields' row spectra src [nf][h][Px] for np planes, whose
 // tables follow each other in H -> dst [np][nf][h][Px] (src itself if np is 1).
 hipError_t launch_asm_columns(const float2 *src, float2 *dst, const float2 *H, uint32_t np, const float2 *tw,

@@ -34,11 +34,12 @@ __global__ void __launch_bounds__(kEncBlock) k_enc_init(const float2 *U, float *
 
 // Row spectra of the rows [nrows][w] that `elem(i, x)` gives (i: element of
 // the array, x: column) -> A [nrows][Px]; grid (rows, fields).
-template <int LG, class F>
+template <int LG, bool TILED, class F>
 __device__ __forceinline__ void rows_of(float2 *A, uint32_t w, uint32_t h, const float2 *tw, C2 *lds, F &&elem) {
   using L = Line<LG>;
-  const uint32_t l = threadIdx.x / L::TPL, t = threadIdx.x % L::TPL;
-  const uint32_t y = blockIdx.x * Rows<LG>::kLines + l;
+  using Lines = Rows<LG, TILED>;
+  const uint32_t l = Lines::line(), t = Lines::pos();
+  const uint32_t y = Lines::group() * Lines::kLines + l;
   const size_t row = (size_t)blockIdx.y * h + y;
   const bool ok = y < h;
   C2 v[L::E];
@@ -47,72 +48,76 @@ __device__ __forceinline__ void rows_of(float2 *A, uint32_t w, uint32_t h, const
     const uint32_t i = t + q * L::TPL;
     v[q] = ok && i < w ? elem(row * w + i) : c2(0.f, 0.f);
   }
-  line_fft<LG, false, true, 1, Rows<LG>::kWave, false>(v, lds + l * L::kLds, TableTwiddles{tw}, t);
+  line_fft<LG, false, true, Lines::kStride, Lines::kWave, false>(v, Lines::lds_of(lds), TableTwiddles{tw}, t);
   if (!ok) return;
-  float2 *dst = A + row * L::N;
+  const uint32_t first = Lines::first_of(t, y, h);
+  float2 *dst = A + (size_t)blockIdx.y * h * L::N;
 #pragma unroll
-  for (uint32_t q = 0; q < L::E; ++q) dst[t + q * L::TPL] = make_float2(v[q].x, v[q].y);
+  for (uint32_t q = 0; q < L::E; ++q) Lines::elem(dst, first, h, q) = make_float2(v[q].x, v[q].y);
 }
 
-template <int LG>
-__global__ void __launch_bounds__(Rows<LG>::W) k_enc_rows_phase(const float *phi, float2 *A, uint32_t w, uint32_t h,
+template <int LG, bool TILED>
+__global__ void __launch_bounds__((Rows<LG, TILED>::W)) k_enc_rows_phase(const float *phi, float2 *A, uint32_t w, uint32_t h,
                                                                 const float2 *tw) {
-  __shared__ C2 lds[Rows<LG>::kLdsElems];
-  rows_of<LG>(A, w, h, tw, lds, [&](size_t i) {
+  __shared__ C2 lds[Rows<LG, TILED>::kLdsElems];
+  rows_of<LG, TILED>(A, w, h, tw, lds, [&](size_t i) {
     float sn, cs;
     sincosf(phi[i], &sn, &cs);
     return c2(cs, sn);
   });
 }
 
-template <int LG>
-__global__ void __launch_bounds__(Rows<LG>::W) k_enc_rows_residual(const float2 *R, const float2 *V, const double2 *s,
-                                                                   float2 *A, uint32_t w, uint32_t h,
-                                                                   const float2 *tw) {
-  __shared__ C2 lds[Rows<LG>::kLdsElems];
+template <int LG, bool TILED>
+__global__ void __launch_bounds__((Rows<LG, TILED>::W))
+    k_enc_rows_residual(const float2 *R, const float2 *V, const double2 *s, float2 *A, uint32_t w, uint32_t h,
+                        const float2 *tw) {
+  __shared__ C2 lds[Rows<LG, TILED>::kLdsElems];
   const double2 sf = s[blockIdx.y];
   const float sr = (float)sf.x, si = (float)sf.y;
-  rows_of<LG>(A, w, h, tw, lds, [&](size_t i) {
+  rows_of<LG, TILED>(A, w, h, tw, lds, [&](size_t i) {
     const float2 v = V[i], x = R[i];
     return c2(x.x - (sr * v.x - si * v.y), x.y - (sr * v.y + si * v.x));
   });
 }
 
-// Inverse FFT of row y of field blockIdx.y of A [nf][h][Px], scaled: v[q], q <
+// Inverse FFT of row y of field blockIdx.y of A [nf][h][Px] (tiled), scaled: v[q], q <
 // E/2, hold elements t + q TPL (of which the first w are wanted).
-template <int LG>
-__device__ __forceinline__ void inverse_row(C2 (&v)[Line<LG>::E], const float2 *A, size_t row, bool ok, float scale,
-                                            const float2 *tw, C2 *lds) {
+template <int LG, bool TILED>
+__device__ __forceinline__ void inverse_row(C2 (&v)[Line<LG>::E], const float2 *A, uint32_t y, uint32_t h,
+                                            float scale, const float2 *tw, C2 *lds) {
   using L = Line<LG>;
-  const uint32_t l = threadIdx.x / L::TPL, t = threadIdx.x % L::TPL;
-  const float2 *src = A + row * L::N;
+  using Lines = Rows<LG, TILED>;
+  const uint32_t l = Lines::line(), t = Lines::pos();
+  const uint32_t first = Lines::first_of(t, y, h);
+  const float2 *src = A + (size_t)blockIdx.y * h * L::N;
 #pragma unroll
   for (uint32_t q = 0; q < L::E; ++q) {
-    const float2 g = ok ? src[t + q * L::TPL] : make_float2(0.f, 0.f);
+    const float2 g = y < h ? Lines::elem(src, first, h, q) : make_float2(0.f, 0.f);
     v[q] = c2(g.x, g.y);
   }
-  line_fft<LG, true, false, 1, Rows<LG>::kWave, false>(v, lds + l * L::kLds, TableTwiddles{tw}, t);
+  line_fft<LG, true, false, Lines::kStride, Lines::kWave, false>(v, Lines::lds_of(lds), TableTwiddles{tw}, t);
 #pragma unroll
   for (uint32_t q = 0; q < L::E / 2; ++q) v[q] = c2(v[q].x * scale, v[q].y * scale);
 }
 
 // R = the inverse row transforms of A; partial sums of conj(V) R (re, im) and
-// |R|^2 over the workgroup's rows, in FP64 -> part[(f gridDim.x + x) 3 + k].
+// |R|^2 over the workgroup's rows, in FP64 -> part[(f gridDim.x + group) 3 + k].
 // SELF: R is V, and only |R|^2 is wanted (the others are 0).
-template <int LG, bool SELF>
-__global__ void __launch_bounds__(Rows<LG>::W) k_enc_ifft_dots(const float2 *A, float2 *R, const float2 *V,
+template <int LG, bool TILED, bool SELF>
+__global__ void __launch_bounds__((Rows<LG, TILED>::W)) k_enc_ifft_dots(const float2 *A, float2 *R, const float2 *V,
                                                                double *part, uint32_t w, uint32_t h, float scale,
                                                                const float2 *tw) {
   using L = Line<LG>;
-  constexpr uint32_t W = Rows<LG>::W;
-  __shared__ C2 lds[Rows<LG>::kLdsElems];
+  using Lines = Rows<LG, TILED>;
+  constexpr uint32_t W = Lines::W;
+  __shared__ C2 lds[Lines::kLdsElems];
   __shared__ double sums[W / 64][3];
-  const uint32_t l = threadIdx.x / L::TPL, t = threadIdx.x % L::TPL;
-  const uint32_t y = blockIdx.x * Rows<LG>::kLines + l;
+  const uint32_t l = Lines::line(), t = Lines::pos();
+  const uint32_t group = Lines::group(), y = group * Lines::kLines + l;
   const size_t row = (size_t)blockIdx.y * h + y;
   const bool ok = y < h;
   C2 v[L::E];
-  inverse_row<LG>(v, A, row, ok, scale, tw, lds);
+  inverse_row<LG, TILED>(v, A, y, h, scale, tw, lds);
   double dr = 0.0, di = 0.0, aa = 0.0;
 #pragma unroll
   for (uint32_t q = 0; q < L::E / 2; ++q) {
@@ -136,7 +141,7 @@ __global__ void __launch_bounds__(Rows<LG>::W) k_enc_ifft_dots(const float2 *A, 
   if (threadIdx.x < 3) {
     double a = 0.0;
     for (uint32_t k = 0; k < W / 64; ++k) a += sums[k][threadIdx.x];
-    part[((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 3 + threadIdx.x] = a;
+    part[((size_t)blockIdx.y * gridDim.x + group) * 3 + threadIdx.x] = a;
   }
 }
 
@@ -168,18 +173,19 @@ __global__ void __launch_bounds__(kEncBlock) k_enc_scale(const double *part, uin
 
 // G = the inverse row transforms of A; g = 2 Im(G conj(exp(i phi))); Adam.
 // FIRST: the moments are zero before this step and are not read.
-template <int LG, bool FIRST>
-__global__ void __launch_bounds__(Rows<LG>::W) k_enc_ifft_adam(const float2 *A, float *phi, float *m, float *v2,
+template <int LG, bool TILED, bool FIRST>
+__global__ void __launch_bounds__((Rows<LG, TILED>::W)) k_enc_ifft_adam(const float2 *A, float *phi, float *m, float *v2,
                                                                uint32_t w, uint32_t h, float scale, float lr,
                                                                float bc1, float bc2, const float2 *tw) {
   using L = Line<LG>;
-  __shared__ C2 lds[Rows<LG>::kLdsElems];
-  const uint32_t l = threadIdx.x / L::TPL, t = threadIdx.x % L::TPL;
-  const uint32_t y = blockIdx.x * Rows<LG>::kLines + l;
+  using Lines = Rows<LG, TILED>;
+  __shared__ C2 lds[Lines::kLdsElems];
+  const uint32_t l = Lines::line(), t = Lines::pos();
+  const uint32_t group = Lines::group(), y = group * Lines::kLines + l;
   const size_t row = (size_t)blockIdx.y * h + y;
   const bool ok = y < h;
   C2 v[L::E];
-  inverse_row<LG>(v, A, row, ok, scale, tw, lds);
+  inverse_row<LG, TILED>(v, A, y, h, scale, tw, lds);
 #pragma unroll
   for (uint32_t q = 0; q < L::E / 2; ++q) {
     const uint32_t x = t + q * L::TPL;
@@ -198,13 +204,13 @@ __global__ void __launch_bounds__(Rows<LG>::W) k_enc_ifft_adam(const float2 *A, 
   }
 }
 
-template <int LG>
-dim3 row_grid(uint32_t nf, uint32_t h) { return dim3((h + Rows<LG>::kLines - 1) / Rows<LG>::kLines, nf); }
+template <int LG, bool TILED>
+dim3 row_grid(uint32_t nf, uint32_t h) { return dim3((h + Rows<LG, TILED>::kLines - 1) / Rows<LG, TILED>::kLines, nf); }
 
-// Rows of w values: f(integral_constant<LG>) for their padded length.
+// Rows of w values of h-row fields: f(integral_constant<LG>, bool_constant<TILED>).
 template <class F>
-hipError_t for_rows(uint32_t w, F &&f) {
-  return with_length(log2u(asm_padded(w)), f) ? hipGetLastError() : hipErrorInvalidValue;
+hipError_t for_rows(uint32_t w, uint32_t h, F &&f) {
+  return with_rows(log2u(asm_padded(w)), asm_tiled(w, h), f) ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 float fft_scale(uint32_t w, uint32_t h) { return 1.0f / ((float)asm_padded(w) * (float)asm_padded(h)); }
@@ -213,7 +219,7 @@ float fft_scale(uint32_t w, uint32_t h) { return 1.0f / ((float)asm_padded(w) * 
 
 uint32_t enc_parts(uint32_t w, uint32_t h) {
   uint32_t n = h;
-  with_length(log2u(asm_padded(w)), [&](auto lg) { n = row_grid<decltype(lg)::value>(1, h).x; });
+  (void)for_rows(w, h, [&](auto lg, auto tiled) { n = row_grid<decltype(lg)::value, decltype(tiled)::value>(1, h).x; });
   return n;
 }
 
@@ -225,9 +231,11 @@ hipError_t launch_enc_init(const float2 *U, float *phi, size_t n, hipStream_t st
 hipError_t launch_enc_target(const float2 *A, float2 *V, double *part, double *vv, const float2 *tw, uint32_t nf,
                              uint32_t w, uint32_t h, hipStream_t st) {
   const float2 *t = tw + 2 * asm_padded(w);
-  hipError_t e = for_rows(w, [&](auto lg) {
+  hipError_t e = for_rows(w, h, [&](auto lg, auto tiled) {
     constexpr int LG = decltype(lg)::value;
-    hipLaunchKernelGGL((k_enc_ifft_dots<LG, true>), row_grid<LG>(nf, h), dim3(Rows<LG>::W), 0, st, A, V, nullptr, part,
+    constexpr bool TILED = decltype(tiled)::value;
+    const dim3 grid = row_grid<LG, TILED>(nf, h), block(Rows<LG, TILED>::W);
+    hipLaunchKernelGGL((k_enc_ifft_dots<LG, TILED, true>), grid, block, 0, st, A, V, nullptr, part,
                        w, h, fft_scale(w, h), t);
   });
   if (e != hipSuccess) return e;
@@ -237,9 +245,11 @@ hipError_t launch_enc_target(const float2 *A, float2 *V, double *part, double *v
 
 hipError_t launch_enc_rows_phase(const float *phi, float2 *A, const float2 *tw, uint32_t nf, uint32_t w, uint32_t h,
                                  hipStream_t st) {
-  return for_rows(w, [&](auto lg) {
+  return for_rows(w, h, [&](auto lg, auto tiled) {
     constexpr int LG = decltype(lg)::value;
-    hipLaunchKernelGGL((k_enc_rows_phase<LG>), row_grid<LG>(nf, h), dim3(Rows<LG>::W), 0, st, phi, A, w, h,
+    constexpr bool TILED = decltype(tiled)::value;
+    const dim3 grid = row_grid<LG, TILED>(nf, h), block(Rows<LG, TILED>::W);
+    hipLaunchKernelGGL((k_enc_rows_phase<LG, TILED>), grid, block, 0, st, phi, A, w, h,
                        tw + 2 * asm_padded(w));
   });
 }
@@ -247,9 +257,11 @@ hipError_t launch_enc_rows_phase(const float *phi, float2 *A, const float2 *tw, 
 hipError_t launch_enc_scale(const float2 *A, float2 *R, const float2 *V, double *part, double *vv, double2 *s,
                             double *rel, const float2 *tw, uint32_t nf, uint32_t w, uint32_t h, hipStream_t st) {
   const float2 *t = tw + 2 * asm_padded(w);
-  hipError_t e = for_rows(w, [&](auto lg) {
+  hipError_t e = for_rows(w, h, [&](auto lg, auto tiled) {
     constexpr int LG = decltype(lg)::value;
-    hipLaunchKernelGGL((k_enc_ifft_dots<LG, false>), row_grid<LG>(nf, h), dim3(Rows<LG>::W), 0, st, A, R, V, part, w, h,
+    constexpr bool TILED = decltype(tiled)::value;
+    const dim3 grid = row_grid<LG, TILED>(nf, h), block(Rows<LG, TILED>::W);
+    hipLaunchKernelGGL((k_enc_ifft_dots<LG, TILED, false>), grid, block, 0, st, A, R, V, part, w, h,
                        fft_scale(w, h), t);
   });
   if (e != hipSuccess) return e;
@@ -259,9 +271,11 @@ hipError_t launch_enc_scale(const float2 *A, float2 *R, const float2 *V, double 
 
 hipError_t launch_enc_rows_residual(const float2 *R, const float2 *V, const double2 *s, float2 *A, const float2 *tw,
                                     uint32_t nf, uint32_t w, uint32_t h, hipStream_t st) {
-  return for_rows(w, [&](auto lg) {
+  return for_rows(w, h, [&](auto lg, auto tiled) {
     constexpr int LG = decltype(lg)::value;
-    hipLaunchKernelGGL((k_enc_rows_residual<LG>), row_grid<LG>(nf, h), dim3(Rows<LG>::W), 0, st, R, V, s, A, w, h,
+    constexpr bool TILED = decltype(tiled)::value;
+    const dim3 grid = row_grid<LG, TILED>(nf, h), block(Rows<LG, TILED>::W);
+    hipLaunchKernelGGL((k_enc_rows_residual<LG, TILED>), grid, block, 0, st, R, V, s, A, w, h,
                        tw + 2 * asm_padded(w));
   });
 }
@@ -269,13 +283,15 @@ hipError_t launch_enc_rows_residual(const float2 *R, const float2 *V, const doub
 hipError_t launch_enc_adam(const float2 *A, float *phi, float *m, float *v, const float2 *tw, uint32_t nf, uint32_t w,
                            uint32_t h, float lr, float bc1, float bc2, bool first, hipStream_t st) {
   const float2 *t = tw + 2 * asm_padded(w);
-  return for_rows(w, [&](auto lg) {
+  return for_rows(w, h, [&](auto lg, auto tiled) {
     constexpr int LG = decltype(lg)::value;
+    constexpr bool TILED = decltype(tiled)::value;
+    const dim3 grid = row_grid<LG, TILED>(nf, h), block(Rows<LG, TILED>::W);
     if (first)
-      hipLaunchKernelGGL((k_enc_ifft_adam<LG, true>), row_grid<LG>(nf, h), dim3(Rows<LG>::W), 0, st, A, phi, m, v, w, h,
+      hipLaunchKernelGGL((k_enc_ifft_adam<LG, TILED, true>), grid, block, 0, st, A, phi, m, v, w, h,
                          fft_scale(w, h), lr, bc1, bc2, t);
     else
-      hipLaunchKernelGGL((k_enc_ifft_adam<LG, false>), row_grid<LG>(nf, h), dim3(Rows<LG>::W), 0, st, A, phi, m, v, w, h,
+      hipLaunchKernelGGL((k_enc_ifft_adam<LG, TILED, false>), grid, block, 0, st, A, phi, m, v, w, h,
                          fft_scale(w, h), lr, bc1, bc2, t);
   });
 }

@@ -221,6 +221,52 @@ struct QuadTwiddles {
   }
 };
 
+// Kept in registers by threads of which each pair of lanes has the same t: the
+// last stage's, which fill the L1 (lane l of the pair keeps pairs 2 j + l, 16
+// registers); the second's are read from the table.
+template <int LG>
+struct PairTwiddles {
+  TableTwiddles table;
+  const float2 *tw;
+  float4 a[4];
+  __device__ __forceinline__ void load(const float2 *t0, uint32_t t) {
+    tw = t0;
+    table.tw = t0;
+    const uint32_t l = threadIdx.x & 1u;
+    const float4 *t4 = reinterpret_cast<const float4 *>(t0);
+    if constexpr (Line<LG>::S16 >= 3)
+      for (uint32_t j = 0; j < 4; ++j) a[j] = t4[128 + (l + 2 * j) * 256 + t % 256u];
+  }
+  template <int L>
+  __device__ __forceinline__ static float lane(float x) {   // x of lane L of the pair
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), L ? 0xF5 : 0xA0, 0xF, 0xF, true));
+  }
+  template <int J>
+  __device__ __forceinline__ static void pair(C2 (&v)[16], const float4 &w, bool inv) {
+    if constexpr (J != 0) {
+      const float s = lane<J & 1>(w.y);
+      v[2 * J] = mul_tw(v[2 * J], lane<J & 1>(w.x), inv ? -s : s);
+    }
+    const float s = lane<J & 1>(w.w);
+    v[2 * J + 1] = mul_tw(v[2 * J + 1], lane<J & 1>(w.z), inv ? -s : s);
+  }
+  template <uint32_t NS>
+  __device__ __forceinline__ void apply(C2 (&v)[16], uint32_t t, bool inv) const {
+    if constexpr (NS == 16) {
+      table.template apply<16>(v, t, inv);
+    } else {
+      float4 w[4];
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j) {   // opaque: as in QuadTwiddles
+        w[j] = a[j];
+        asm volatile("" : "+v"(w[j].x), "+v"(w[j].y), "+v"(w[j].z), "+v"(w[j].w));
+      }
+      pair<0>(v, w[0], inv); pair<1>(v, w[0], inv); pair<2>(v, w[1], inv); pair<3>(v, w[1], inv);
+      pair<4>(v, w[2], inv); pair<5>(v, w[2], inv); pair<6>(v, w[3], inv); pair<7>(v, w[3], inv);
+    }
+  }
+};
+
 // The XR of dft16 in the first and third, and in the second radix-16 stage
 // (m = 1, 2, 3; in 4096-point columns m = 1, 3, inversely also 9).
 template <int LG, bool COLS, bool INV>
@@ -289,15 +335,65 @@ __device__ __forceinline__ void line_fft(C2 (&v)[Line<LG>::E], C2 *x, const Twid
   }
 }
 
-// Threads of a row kernel's workgroup and the lines it works on (t fastest:
-// consecutive threads on consecutive elements of a row).
-template <int LG>
+// Element at a byte offset from a uniform base: a scalar base and a 32-bit
+// offset register. (The offset goes through an empty asm so that its
+// extension to 64 bits stays beside the access; hoisted, every access would
+// add two registers' worth of address instead.)
+__device__ __forceinline__ const float2 &at(const float2 *p, uint32_t off) {
+  asm volatile("" : "+v"(off));
+  return *(const float2 *)((const char *)p + off);
+}
+__device__ __forceinline__ float2 &at(float2 *p, uint32_t off) {
+  asm volatile("" : "+v"(off));
+  return *(float2 *)((char *)p + off);
+}
+
+// Row spectra [h][n] of a field, in the plain order or (TILED) in tiles of kTile
+// columns: element (y, x) at ((x / kTile) h + y) kTile + x mod kTile (asm.hip says
+// when and why).
+constexpr uint32_t kTile = 8;
+
+// Threads of a row kernel's workgroup and the lines it works on. In plain order
+// consecutive threads are on consecutive elements of a row; of tiled rows of 2048
+// points or more a workgroup takes two, in turn over the threads, so that it has
+// whole 128-byte pieces of the tiles.
+template <int LG, bool TILED>
 struct Rows {
-  static constexpr uint32_t W = Line<LG>::TPL < 64 ? 64 : Line<LG>::TPL;
-  static constexpr uint32_t kLines = W / Line<LG>::TPL;
-  static constexpr bool kWave = Line<LG>::TPL <= 64;
-  static constexpr uint32_t kLdsElems = Line<LG>::S16 >= 1 && LG > 4 ? kLines * Line<LG>::kLds : 1;
+  using L = Line<LG>;
+  static constexpr bool kPairs = TILED && (LG == 11 || LG == 12);
+  static constexpr uint32_t W = kPairs ? 2 * L::TPL : L::TPL < 64 ? 64 : L::TPL;
+  static constexpr uint32_t kLines = W / L::TPL;
+  static constexpr uint32_t kStride = kPairs ? kLines : 1;   // of a line's elements in LDS
+  static constexpr bool kWave = L::TPL <= 64;
+  static constexpr uint32_t kLdsElems = L::S16 >= 1 && LG > 4 ? kLines * L::kLds : 1;
+  // this workgroup among its field's: tiled, each XCD takes one range of rows,
+  // so that the rows that share a line of the cache meet in one L2
+  __device__ __forceinline__ static uint32_t group();
+  // this thread's line of the workgroup, its place in the line, the line's LDS
+  __device__ __forceinline__ static uint32_t line() { return kPairs ? threadIdx.x % kLines : threadIdx.x / L::TPL; }
+  __device__ __forceinline__ static uint32_t pos() { return kPairs ? threadIdx.x / kLines : threadIdx.x % L::TPL; }
+  __device__ __forceinline__ static C2 *lds_of(C2 *lds) { return lds + line() * (kPairs ? 1 : L::kLds); }
+  // element t + q TPL of row y of a field [h][N]: first = first_of(t, y, h)
+  __device__ __forceinline__ static uint32_t first_of(uint32_t t, uint32_t y, uint32_t h) {
+    return TILED ? ((t / kTile) * h + y) * kTile + t % kTile : y * L::N + t;
+  }
+  template <class P>
+  __device__ __forceinline__ static auto &elem(P *field, uint32_t first, uint32_t h, uint32_t q) {
+    if constexpr (TILED) return at(field + (size_t)(q * L::TPL) * h, first * 8);
+    else return (field + first)[q * L::TPL];
+  }
 };
+
+// Workgroup b of g, renumbered so that each of the 8 XCDs (workgroups are
+// dealt to them in turn) takes one contiguous range.
+__device__ __forceinline__ uint32_t xcd_group(uint32_t b, uint32_t g) {
+  return g % 8u ? b : (b % 8u) * (g / 8u) + b / 8u;
+}
+
+template <int LG, bool TILED>
+__device__ __forceinline__ uint32_t Rows<LG, TILED>::group() {
+  return TILED ? xcd_group(blockIdx.x, gridDim.x) : blockIdx.x;
+}
 
 inline uint32_t log2u(uint32_t n) {
   uint32_t l = 0;
@@ -324,6 +420,18 @@ inline bool with_length(uint32_t lg, F &&f) {
     case 13: f(std::integral_constant<int, 13>{}); return true;
     default: return false;
   }
+}
+
+// f(integral_constant<LG>, bool_constant<TILED>) for rows of length 2^lg.
+constexpr int kTiledLg = 9;  // shortest tiled row: kTile divides its TPL, and a tile is a fraction of it
+template <class F>
+inline bool with_rows(uint32_t lg, bool tiled, F &&f) {
+  return with_length(lg, [&](auto l) {
+    if constexpr (decltype(l)::value >= kTiledLg) {
+      if (tiled) { f(l, std::true_type{}); return; }
+    }
+    f(l, std::false_type{});
+  });
 }
 
 }  // namespace fft

@@ -1738,7 +1738,7 @@ hpt_status hpt_encode_phase(hpt_ctx *C, const void *d_fields, uint32_t n_fields,
     const uint32_t nf = std::min(chunk, n_fields - f0);
     const float2 *U = (const float2 *)d_fields + (size_t)f0 * hw;
     float *phi = (float *)d_phase + (size_t)f0 * hw;
-    e = launch_asm_rows(U, A, tw, nf * height, width, st);
+    e = launch_asm_rows(U, A, tw, nf, width, height, st);
     if (e == hipSuccess) e = columns(false, nf);
     if (e == hipSuccess) e = launch_enc_target(A, V, part, vv, tw, nf, width, height, st);
     if (e == hipSuccess && !warm) e = launch_enc_init(U, phi, (size_t)nf * hw, st);
@@ -1810,7 +1810,8 @@ hpt_status hpt_reconstruct(hpt_ctx *C, const void *d_fields, uint32_t n_ch, uint
   for (uint32_t c = 0; c < n_ch && e == hipSuccess; ++c) {
     for (uint32_t t0 = 0; t0 < T && e == hipSuccess; t0 += chunk) {
       const uint32_t nf = std::min(chunk, T - t0);
-      e = launch_asm_rows((const float2 *)d_fields + ((size_t)c * T + t0) * field, S, tw, nf * height, width, C->aux);
+      e = launch_asm_rows((const float2 *)d_fields + ((size_t)c * T + t0) * field, S, tw, nf, width, height,
+                          C->aux);
       for (uint32_t p0 = 0; p0 < n_planes && e == hipSuccess; p0 += group) {
         const uint32_t np = std::min(group, n_planes - p0);
         if (t0 == 0 || group < n_planes)   // else the tables of the channel are in place
