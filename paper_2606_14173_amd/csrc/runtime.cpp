@@ -1743,7 +1743,8 @@ hpt_status hpt_encode_phase(hpt_ctx *C, const void *d_fields, uint32_t n_fields,
     if (e == hipSuccess) e = launch_enc_target(A, V, part, vv, tw, nf, width, height, st);
     if (e == hipSuccess && !warm) e = launch_enc_init(U, phi, (size_t)nf * hw, st);
     for (uint32_t k = 1; k <= iterations + 1 && e == hipSuccess; ++k) {
-      e = launch_enc_rows_phase(phi, A, tw, nf, width, height, st);
+      // A holds the row spectra of exp(i phi): made here, later by the step before
+      if (k == 1) e = launch_enc_rows_phase(phi, A, tw, nf, width, height, st);
       if (e == hipSuccess) e = columns(false, nf);
       if (e == hipSuccess) e = launch_enc_scale(A, R, V, part, vv, sc, rel + f0, tw, nf, width, height, st);
       if (k > iterations) break;  // the final loss
