@@ -50,15 +50,47 @@ namespace {
 
 using namespace fft;
 
-// Forward FFT of row (f, y) of in [nf][h][w], zero-padded to Px -> A [nf][h][Px].
+// The transfer function's table T[ky][kx] = H at |f_x| = kx / (Px d), |f_y| = ky /
+// (Py d), kx < nx = Px/2 + 1, ky < ny = Py/2 + 1.
+struct TransferTable {
+  float2 *T;
+  uint32_t nx, ny;
+  AsmParams P;
+  __device__ __forceinline__ void fill(uint32_t i) const {
+    if (i >= nx * ny) return;
+    const uint32_t ky = i / nx, kx = i - ky * nx;
+    const double fx = (double)kx * P.dfx, fy = (double)ky * P.dfy;
+    const double f2 = fx * fx + fy * fy;
+    float2 v = make_float2(0.f, 0.f);
+    if ((!P.band_limit || (fx <= P.lim_x && fy <= P.lim_y)) && f2 < P.inv_lam2 && (P.pupil2 <= 0.0 || f2 <= P.pupil2)) {
+      // z sqrt(1/lambda^2 - f^2) = z/lambda - z f^2 / (1/lambda + sqrt(1/lambda^2 - f^2)),
+      // the first term reduced modulo 1 on the host
+      const double rev = P.z_rev_frac - P.z * f2 / (P.inv_lam + sqrt(P.inv_lam2 - f2));
+      const double fr = rev - floor(rev);
+      double sn, cs;
+      sincospi(2.0 * fr, &sn, &cs);
+      v = make_float2((float)cs, (float)sn);
+    }
+    T[i] = v;
+  }
+};
+
+// Forward FFT of row (f, y) of in [nf][h][w], zero-padded to Px -> A [nf][h][Px], on
+// the first `groups` workgroups; the others fill T, which saves a small call a
+// launch (two 64 x 64 fields 31 -> 28.5 us).
 template <int LG, bool TILED>
 __global__ void __launch_bounds__((Rows<LG, TILED>::W))
-    k_fft_rows(const float2 *in, float2 *A, uint32_t w, uint32_t h, uint32_t nrows, const float2 *tw) {
+    k_fft_rows(const float2 *in, float2 *A, uint32_t w, uint32_t h, uint32_t nrows, const float2 *tw, uint32_t groups,
+               TransferTable T) {
   using L = Line<LG>;
   using Lines = Rows<LG, TILED>;
   __shared__ C2 lds[Lines::kLdsElems];
+  if (blockIdx.x >= groups) {
+    T.fill((blockIdx.x - groups) * Lines::W + threadIdx.x);
+    return;
+  }
   const uint32_t l = Lines::line(), t = Lines::pos();
-  const uint32_t row = Lines::group() * Lines::kLines + l;  // f * h + y
+  const uint32_t row = Lines::group(groups) * Lines::kLines + l;  // f * h + y
   const bool ok = row < nrows;
   const float2 *src = in + (size_t)row * w;
   C2 v[L::E];
@@ -196,7 +228,7 @@ __global__ void __launch_bounds__((Rows<LG, TILED>::W))
   using Lines = Rows<LG, TILED>;
   __shared__ C2 lds[Lines::kLdsElems];
   const uint32_t l = Lines::line(), t = Lines::pos();
-  const uint32_t row = Lines::group() * Lines::kLines + l;
+  const uint32_t row = Lines::group(gridDim.x) * Lines::kLines + l;
   const bool ok = row < nrows;
   const uint32_t f = TILED ? row / h : row, y = TILED ? row - f * h : 0u, first = Lines::first_of(t, y, h);
   const float2 *src = A + (size_t)f * (TILED ? h : 1u) * L::N;
@@ -228,7 +260,7 @@ __global__ void __launch_bounds__((Rows<LG, TILED>::W)) k_ifft_rows_intensity(co
   using Lines = Rows<LG, TILED>;
   __shared__ C2 lds[Lines::kLdsElems];
   const uint32_t l = Lines::line(), t = Lines::pos();
-  const uint32_t y = Lines::group() * Lines::kLines + l;
+  const uint32_t y = Lines::group(gridDim.x) * Lines::kLines + l;
   const bool ok = y < h;
   const uint32_t first = Lines::first_of(t, y, h);
   const float2 *Ap = A + (size_t)blockIdx.y * nf * h * L::N;
@@ -258,25 +290,8 @@ __global__ void __launch_bounds__((Rows<LG, TILED>::W)) k_ifft_rows_intensity(co
   }
 }
 
-// T[ky][kx] = H at |f_x| = kx / (Px d), |f_y| = ky / (Py d), kx <= Px/2, ky <= Py/2.
-__global__ void __launch_bounds__(256) k_transfer(float2 *T, uint32_t nx, uint32_t ny, AsmParams P) {
-  const uint32_t i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= nx * ny) return;
-  const uint32_t ky = i / nx, kx = i - ky * nx;
-  const double fx = (double)kx * P.dfx, fy = (double)ky * P.dfy;
-  const double f2 = fx * fx + fy * fy;
-  float2 v = make_float2(0.f, 0.f);
-  if ((!P.band_limit || (fx <= P.lim_x && fy <= P.lim_y)) && f2 < P.inv_lam2 && (P.pupil2 <= 0.0 || f2 <= P.pupil2)) {
-    // z sqrt(1/lambda^2 - f^2) = z/lambda - z f^2 / (1/lambda + sqrt(1/lambda^2 - f^2)),
-    // the first term reduced modulo 1 on the host
-    const double rev = P.z_rev_frac - P.z * f2 / (P.inv_lam + sqrt(P.inv_lam2 - f2));
-    const double fr = rev - floor(rev);
-    double sn, cs;
-    sincospi(2.0 * fr, &sn, &cs);
-    v = make_float2((float)cs, (float)sn);
-  }
-  T[i] = v;
-}
+// Where no row pass goes with it.
+__global__ void __launch_bounds__(256) k_transfer(TransferTable T) { T.fill(blockIdx.x * 256 + threadIdx.x); }
 
 // Twiddles of every length, in the order of fft.hpp: entry e of length n =
 // 2^lg is exp(-2 pi i m / n) (FP64, rounded).
@@ -355,23 +370,34 @@ size_t asm_transfer_elems(uint32_t w, uint32_t h) {
 // Whether row spectra are tiled: see the head of this file.
 bool asm_tiled(uint32_t w, uint32_t h) { return asm_padded(h) >= 2048 && asm_padded(w) >= 1u << kTiledLg; }
 
+static TransferTable transfer_table(float2 *T, uint32_t w, uint32_t h, const AsmParams &P) {
+  return {T, asm_padded(w) / 2 + 1, asm_padded(h) / 2 + 1, P};
+}
+
 hipError_t launch_asm_transfer(float2 *T, uint32_t w, uint32_t h, const AsmParams &P, hipStream_t st) {
-  const uint32_t nx = asm_padded(w) / 2 + 1, ny = asm_padded(h) / 2 + 1;
-  hipLaunchKernelGGL(k_transfer, dim3((nx * ny + 255) / 256), dim3(256), 0, st, T, nx, ny, P);
+  const TransferTable table = transfer_table(T, w, h, P);
+  hipLaunchKernelGGL(k_transfer, dim3((table.nx * table.ny + 255) / 256), dim3(256), 0, st, table);
   return hipGetLastError();
 }
 
-hipError_t launch_asm_rows(const float2 *in, float2 *A, const float2 *tw, uint32_t nf, uint32_t w, uint32_t h,
-                           hipStream_t st) {
+// table.nx 0: none.
+static hipError_t launch_rows(const float2 *in, float2 *A, const TransferTable &table, const float2 *tw, uint32_t nf,
+                              uint32_t w, uint32_t h, hipStream_t st) {
   const uint32_t px = asm_padded(w), nrows = nf * h;
   const bool known = with_rows(log2u(px), asm_tiled(w, h), [&](auto lg, auto tiled) {
     constexpr int LG = decltype(lg)::value;
     constexpr bool TILED = decltype(tiled)::value;
     constexpr uint32_t n = Rows<LG, TILED>::kLines, W = Rows<LG, TILED>::W;
-    hipLaunchKernelGGL((k_fft_rows<LG, TILED>), dim3((nrows + n - 1) / n), dim3(W), 0, st, in, A, w,
-                       h, nrows, tw + 2 * px);
+    const uint32_t groups = (nrows + n - 1) / n, more = (table.nx * table.ny + W - 1) / W;
+    hipLaunchKernelGGL((k_fft_rows<LG, TILED>), dim3(groups + more), dim3(W), 0, st, in, A, w, h, nrows, tw + 2 * px,
+                       groups, table);
   });
   return known ? hipGetLastError() : hipErrorInvalidValue;
+}
+
+hipError_t launch_asm_rows(const float2 *in, float2 *A, const float2 *tw, uint32_t nf, uint32_t w, uint32_t h,
+                           hipStream_t st) {
+  return launch_rows(in, A, TransferTable{}, tw, nf, w, h, st);
 }
 
 hipError_t launch_asm_columns(const float2 *src, float2 *dst, const float2 *H, uint32_t np, const float2 *tw,
@@ -390,11 +416,11 @@ hipError_t launch_asm_columns(const float2 *src, float2 *dst, const float2 *H, u
   return known ? hipGetLastError() : hipErrorInvalidValue;
 }
 
-hipError_t launch_asm(const float2 *in, float2 *out, float2 *A, const float2 *H, const float2 *tw, uint32_t nf,
-                      uint32_t w, uint32_t h, hipStream_t st) {
+hipError_t launch_asm(const float2 *in, float2 *out, float2 *A, float2 *H, const AsmParams *P, const float2 *tw,
+                      uint32_t nf, uint32_t w, uint32_t h, hipStream_t st) {
   if (nf == 0 || w == 0 || h == 0) return hipErrorInvalidValue;
   const uint32_t px = asm_padded(w), py = asm_padded(h), nrows = nf * h;
-  hipError_t e = launch_asm_rows(in, A, tw, nf, w, h, st);
+  hipError_t e = launch_rows(in, A, P ? transfer_table(H, w, h, *P) : TransferTable{}, tw, nf, w, h, st);
   if (e == hipSuccess) e = launch_asm_columns(A, A, H, 1, tw, nf, w, h, st);
   if (e != hipSuccess) return e;
   const bool known = with_rows(log2u(px), asm_tiled(w, h), [&](auto lg, auto tiled) {

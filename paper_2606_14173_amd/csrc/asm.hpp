@@ -38,15 +38,17 @@ hipError_t asm_device(int device, AsmDevice *out);
 // Transfer function of P for fields of w x h, tabulated over a quarter of the
 // frequency plane (asm_transfer_elems complex64: never more than h Px + Px +
 // Py).
-// Whether the row spectra of w x h fields lie in tiles (fft.hpp).
-bool asm_tiled(uint32_t w, uint32_t h);
 size_t asm_transfer_elems(uint32_t w, uint32_t h);
 hipError_t launch_asm_transfer(float2 *T, uint32_t w, uint32_t h, const AsmParams &P, hipStream_t st);
 
 // nf fields in [nf][h][w] -> out (may alias in); A: scratch of
-// nf * h * asm_padded(w) complex64; H: the table above.
-hipError_t launch_asm(const float2 *in, float2 *out, float2 *A, const float2 *H, const float2 *tw, uint32_t nf,
-                      uint32_t w, uint32_t h, hipStream_t st);
+// nf * h * asm_padded(w) complex64; H: the table above, which P (if not null) has
+// filled on the way.
+hipError_t launch_asm(const float2 *in, float2 *out, float2 *A, float2 *H, const AsmParams *P, const float2 *tw,
+                      uint32_t nf, uint32_t w, uint32_t h, hipStream_t st);
+
+// Whether the row spectra of w x h fields lie in tiles (fft.hpp).
+bool asm_tiled(uint32_t w, uint32_t h);
 
 // The passes by themselves. Row spectra of nf fields [nf][h][w] -> A [nf][h][Px],
 // in tiles if asm_tiled, as all row spectra are.

@@ -55,7 +55,7 @@ template <int LG, bool TILED, class F>
 __device__ __forceinline__ void rows_of(float2 *A, uint32_t w, uint32_t h, const float2 *tw, C2 *lds, F &&elem) {
   using L = Line<LG>;
   using Lines = Rows<LG, TILED>;
-  const uint32_t t = Lines::pos(), y = Lines::group() * Lines::kLines + Lines::line();
+  const uint32_t t = Lines::pos(), y = Lines::group(gridDim.x) * Lines::kLines + Lines::line();
   const size_t row = (size_t)blockIdx.y * h + y;
   C2 v[L::E];
 #pragma unroll
@@ -123,7 +123,7 @@ __global__ void __launch_bounds__((Rows<LG, TILED>::W)) k_enc_ifft_dots(const fl
   __shared__ C2 lds[Lines::kLdsElems];
   __shared__ double sums[W / 64][3];
   const uint32_t l = Lines::line(), t = Lines::pos();
-  const uint32_t group = Lines::group(), y = group * Lines::kLines + l;
+  const uint32_t group = Lines::group(gridDim.x), y = group * Lines::kLines + l;
   const size_t row = (size_t)blockIdx.y * h + y;
   const bool ok = y < h;
   C2 v[L::E];
@@ -184,8 +184,8 @@ __global__ void __launch_bounds__(kEncBlock) k_enc_scale(const double *part, uin
 // G = the inverse row transforms of A; g = 2 Im(G conj(exp(i phi))); Adam; then
 // the row spectra of the new exp(i phi) -> A, which the next step (or the final
 // loss) starts with. One kernel for both: the row is in registers, and a step has
-// one launch and one reading of phi less (20 steps on 24 fields of 300 x 200 1.07 ->
-// 1.015 ms, of 1920 x 1080 79.7 -> 78.8).
+// one launch and one reading of phi less (20 steps on 3 fields of 300 x 200 1.07 ->
+// 1.015 ms, on 24 of 1920 x 1080 79.7 -> 78.8).
 // FIRST: the moments are zero before this step and are not read.
 template <int LG, bool TILED, bool FIRST>
 __global__ void __launch_bounds__((Rows<LG, TILED>::W))
@@ -195,7 +195,7 @@ __global__ void __launch_bounds__((Rows<LG, TILED>::W))
   using Lines = Rows<LG, TILED>;
   __shared__ C2 lds[Lines::kLdsElems];
   const uint32_t l = Lines::line(), t = Lines::pos();
-  const uint32_t group = Lines::group(), y = group * Lines::kLines + l;
+  const uint32_t group = Lines::group(gridDim.x), y = group * Lines::kLines + l;
   const size_t row = (size_t)blockIdx.y * h + y;
   const bool ok = y < h;
   C2 v[L::E];

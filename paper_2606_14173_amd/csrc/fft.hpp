@@ -368,7 +368,7 @@ struct Rows {
   static constexpr uint32_t kLdsElems = L::S16 >= 1 && LG > 4 ? kLines * L::kLds : 1;
   // this workgroup among its field's: tiled, each XCD takes one range of rows,
   // so that the rows that share a line of the cache meet in one L2
-  __device__ __forceinline__ static uint32_t group();
+  __device__ __forceinline__ static uint32_t group(uint32_t groups);
   // this thread's line of the workgroup, its place in the line, the line's LDS
   __device__ __forceinline__ static uint32_t line() { return kPairs ? threadIdx.x % kLines : threadIdx.x / L::TPL; }
   __device__ __forceinline__ static uint32_t pos() { return kPairs ? threadIdx.x / kLines : threadIdx.x % L::TPL; }
@@ -391,8 +391,8 @@ __device__ __forceinline__ uint32_t xcd_group(uint32_t b, uint32_t g) {
 }
 
 template <int LG, bool TILED>
-__device__ __forceinline__ uint32_t Rows<LG, TILED>::group() {
-  return TILED ? xcd_group(blockIdx.x, gridDim.x) : blockIdx.x;
+__device__ __forceinline__ uint32_t Rows<LG, TILED>::group(uint32_t groups) {
+  return TILED ? xcd_group(blockIdx.x, groups) : blockIdx.x;
 }
 
 inline uint32_t log2u(uint32_t n) {

@@ -1624,12 +1624,11 @@ hpt_status hpt_asm_propagate(hpt_ctx *C, const void *d_in, void *d_out, uint32_t
   }
   float2 *H = S.take<float2>(h_elems), *A = S.take<float2>((size_t)chunk * height * px);
   hipError_t e = after_caller(C->aux, hip_stream);
-  if (e == hipSuccess) e = launch_asm_transfer(H, width, height, P, C->aux);
   const size_t field = (size_t)width * height;
   for (uint32_t f0 = 0; f0 < n_fields && e == hipSuccess; f0 += chunk) {
     uint32_t nf = std::min(chunk, n_fields - f0);
-    e = launch_asm((const float2 *)d_in + f0 * field, (float2 *)d_out + f0 * field, A, H, C->fft.tw, nf, width, height,
-                   C->aux);
+    e = launch_asm((const float2 *)d_in + f0 * field, (float2 *)d_out + f0 * field, A, H, f0 ? nullptr : &P,
+                   C->fft.tw, nf, width, height, C->aux);
   }
   if (e == hipSuccess) e = hipStreamSynchronize(C->aux);
   else (void)hipStreamSynchronize(C->aux);  // launches already queued still use the scratch
@@ -1664,12 +1663,12 @@ hpt_status hpt_asm_propagate_noalloc(hpt_ctx *C, const void *d_in, void *d_out, 
   float2 *H = C->fft.scratch, *A = H + up(asm_transfer_elems(width, height));
   hipStream_t st = hip_stream ? (hipStream_t)hip_stream : C->aux;
   (void)hipSetDevice(C->device);
-  hipError_t e = launch_asm_transfer(H, width, height, P, st);
+  hipError_t e = hipSuccess;
   const size_t field = (size_t)width * height;
   for (uint32_t f0 = 0; f0 < n_fields && e == hipSuccess; f0 += chunk) {
     const uint32_t nf = std::min(chunk, n_fields - f0);
-    e = launch_asm((const float2 *)d_in + f0 * field, (float2 *)d_out + f0 * field, A, H, C->fft.tw, nf, width, height,
-                   st);
+    e = launch_asm((const float2 *)d_in + f0 * field, (float2 *)d_out + f0 * field, A, H, f0 ? nullptr : &P,
+                   C->fft.tw, nf, width, height, st);
   }
   if (e == hipSuccess && !hip_stream) e = hipStreamSynchronize(st);
   if (e != hipSuccess) return fail(HPT_EDEVICE, std::string("propagation failed: ") + hipGetErrorString(e));
