@@ -374,7 +374,7 @@ __device__ __forceinline__ NodeWords load_node(const Stack &S, GF4 N, int32_t no
 
 // Advance this lane by one round: descend inner nodes, postponing the first
 // leaf reached and continuing with the next stack entry, until all but at
-// most kTraceStragglers lanes of the wave hold a leaf or have nothing left to
+// most `stragglers` lanes of the wave hold a leaf or have nothing left to
 // descend; then test the postponed leaf (Aila and Laine's speculative
 // "while-while", which keeps lanes descending instead of idling while others
 // look for a leaf; lanes still descending carry on next round). Leaves
@@ -382,7 +382,7 @@ __device__ __forceinline__ NodeWords load_node(const Stack &S, GF4 N, int32_t no
 // make the result independent of the order. COUNT adds node visits and
 // primitive tests to nv / nt.
 template <bool COUNT>
-__device__ __forceinline__ void trav_step(Trav &T, const Bvh &V, const Stack &St, uint32_t &nv, uint32_t &nt) {
+__device__ __forceinline__ void trav_step(Trav &T, const Bvh &V, const Stack &St, uint32_t &nv, uint32_t &nt, int stragglers) {
   const Slabs sl = slabs_of(T.r, V.scale);
   int32_t node = T.node;
   int sp = T.sp;
@@ -404,11 +404,11 @@ __device__ __forceinline__ void trav_step(Trav &T, const Bvh &V, const Stack &St
       node = kPop;
     }
     if (node == kPop) node = pop(St, sp);
-    // leave the descent once at most kTraceStragglers lanes are still
+    // leave the descent once at most `stragglers` lanes are still
     // looking for a leaf (waiting for all of them leaves most of the wave
     // idle); the stragglers resume where they are in the next step
     const uint32_t looking = (uint32_t)node | ((uint32_t)leaf & 0x80000000u);
-    if (count_lanes(__builtin_amdgcn_ballot_w64(looking < (uint32_t)kPop)) <= kTraceStragglers) break;
+    if (count_lanes(__builtin_amdgcn_ballot_w64(looking < (uint32_t)kPop)) <= stragglers) break;
   }
   // the leaf to test now: the postponed one, or one just popped
   const int32_t now = leaf < 0 ? leaf : node;

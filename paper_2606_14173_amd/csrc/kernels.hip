@@ -581,7 +581,12 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(COU
   }
   const uint32_t cls = blockIdx.x % kClaimClasses;
   uint32_t *claim = B.claims + ((uint32_t)q * kClaimClasses + cls) * kClaimStride;
-  const uint32_t n_chunks = (n + kTraceChunk - 1) / kTraceChunk;
+  // a queue that is short of a chunk for every wave is cut finer: fewer rays wait
+  // for each other, and a node costs a wave fewer accesses
+  uint32_t chunk = kTraceChunk;
+  const uint32_t each = n / (gridDim.x * (kBlock / 64));   // rays a wave
+  while (chunk > kTraceChunkMin && chunk / 2 >= each) chunk /= 2;
+  const uint32_t n_chunks = (n + chunk - 1) / chunk;
   const uint32_t lane = __lane_id();
   const Stack St{(LdsI32)(stack + kBlock + threadIdx.x), kBlock,
                  (GlbI32)(B.stack_spill + xcd_block() * blockDim.x + threadIdx.x), B.spill_threads,
@@ -604,8 +609,8 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(COU
       if (j >= n_chunks) {
         more = false;
       } else {
-        next = j * (uint32_t)kTraceChunk;
-        end = min(n, next + (uint32_t)kTraceChunk);
+        next = j * chunk;
+        end = min(n, next + chunk);
       }
     }
     // refill idle lanes from the chunk, in lane order, once kTraceRefill of
@@ -645,9 +650,10 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(COU
       if (!more) break;
       continue;
     }
+    const int stragglers = count_lanes(__ballot(i >= 0)) / kTraceStragglers;
     if (i >= 0 && !(NEE && waits)) {
       const uint32_t nv0 = nv, nt0 = nt;
-      if (T.node != kDone) trav_step<COUNT>(T, V, St, nv, nt);
+      if (T.node != kDone) trav_step<COUNT>(T, V, St, nv, nt, stragglers);
       const bool query = NEE && ts < 0.f;
       if (query) {
         nv = nv0; nt = nt0;   // (counted are the rays)
