@@ -382,7 +382,8 @@ __device__ __forceinline__ NodeWords load_node(const Stack &S, GF4 N, int32_t no
 // make the result independent of the order. COUNT adds node visits and
 // primitive tests to nv / nt.
 template <bool COUNT>
-__device__ __forceinline__ void trav_step(Trav &T, const Bvh &V, const Stack &St, uint32_t &nv, uint32_t &nt, int stragglers) {
+__device__ __forceinline__ void trav_step(Trav &T, const Bvh &V, const Stack &St, uint32_t &nv, uint32_t &nt,
+                                          int stragglers) {
   const Slabs sl = slabs_of(T.r, V.scale);
   int32_t node = T.node;
   int sp = T.sp;

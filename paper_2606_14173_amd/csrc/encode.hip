@@ -67,8 +67,8 @@ __device__ __forceinline__ void rows_of(float2 *A, uint32_t w, uint32_t h, const
 }
 
 template <int LG, bool TILED>
-__global__ void __launch_bounds__((Rows<LG, TILED>::W)) k_enc_rows_phase(const float *phi, float2 *A, uint32_t w, uint32_t h,
-                                                                const float2 *tw) {
+__global__ void __launch_bounds__((Rows<LG, TILED>::W))
+    k_enc_rows_phase(const float *phi, float2 *A, uint32_t w, uint32_t h, const float2 *tw) {
   __shared__ C2 lds[Rows<LG, TILED>::kLdsElems];
   rows_of<LG, TILED>(A, w, h, tw, lds, [&](size_t i) {
     float sn, cs;

@@ -556,7 +556,8 @@ __device__ __forceinline__ Bvh shared_bvh_of(const SceneDev &S) {
 // 25.6 to 23.4 ms. (A mixed batch's top nodes, shared out in LDS, gained it
 // nothing.)
 template <bool COUNT, bool ONE, bool NEE>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(COUNT ? 6 : 7))) k_trace(BatchDev B, int q, int dense) {
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(COUNT ? 6 : 7)))
+    k_trace(BatchDev B, int q, int dense) {
   // issue priority over the previous batch's accumulation waves that share
   // the SIMDs (the traversal is on the step's critical path, the
   // accumulation beside it is not)

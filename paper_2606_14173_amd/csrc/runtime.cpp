@@ -532,7 +532,8 @@ hpt_status launch_batch(hpt_ctx *C, int si, int prev) {
   for (size_t k = 0; k < P.size(); ++k) {
     const Unit &u = P[k].job->units[P[k].unit];
     UnitDev &d = L.h_units[k];
-    d.kind = (uint16_t)u.kind; d.ch = (uint16_t)u.ch; d.s_n_m = div_magic(u.s_n); d.p_lo = u.p_lo; d.p_n = u.p_n; d.s_lo = u.s_lo; d.s_n = u.s_n;
+    d.kind = (uint16_t)u.kind; d.ch = (uint16_t)u.ch; d.p_lo = u.p_lo; d.p_n = u.p_n; d.s_lo = u.s_lo; d.s_n = u.s_n;
+    d.s_n_m = div_magic(u.s_n);
     d.slot_base = slot; d.acc_base = acc; d.job = P[k].job->dev; d.scene = P[k].job->scene->dev;
     const JobDev &J = P[k].job->host;
     slot += u.p_n * u.s_n;
@@ -580,7 +581,8 @@ hpt_status launch_batch(hpt_ctx *C, int si, int prev) {
                    B.n_units <= shade_lds_units();
   for (uint32_t it = 0; it <= max_b; ++it) {
     int q = (int)(it & 1u);
-    timed_launch(L, HPT_K_TRACE, S, e, [&] { return launch_trace(B, q, it == 0 || B.dense, profile >= 2, it > 0 && nee, S); });
+    timed_launch(L, HPT_K_TRACE, S, e,
+                 [&] { return launch_trace(B, q, it == 0 || B.dense, profile >= 2, it > 0 && nee, S); });
     timed_launch(L, HPT_K_SHADE, S, e, [&] { return launch_shade(B, q, it, L.has_ext, uni, S); });
     // the last pass ends every path (interaction max_b + 1 exceeds the
     // budget), so only the earlier ones leave rays to order
