@@ -268,28 +268,20 @@ bool build_bvh(const float *tri, uint32_t n_tri, const float *sph, uint32_t n_sp
 
 namespace {
 
-// Bits of the smallest binary16 >= v for v >= 0 (never subnormal), of the
-// largest <= v otherwise.
-uint16_t half_up(double v) {
-  if (v == 0.0) return 0;
-  if (v > 65504.0) return 0x7C00;
-  int e;
-  std::frexp(v, &e);               // v in [2^(e-1), 2^e)
-  if (e - 1 < -14) return 0x0400;  // 2^-14
-  uint32_t m = (uint32_t)std::ceil(std::ldexp(v, 11 - e));  // [1024, 2048]
-  if (m == 2048) { m = 1024; ++e; }
-  return e - 1 > 15 ? 0x7C00 : (uint16_t)(((e + 14) << 10) | (m - 1024));
+// |v| as binary16 bits, rounded away from zero (never to a subnormal) or towards
+// it. (From the bits of v and without branches: with frexp and ldexp packing took
+// a tenth of the time that building the nodes does.)
+inline uint32_t half_of(double v, bool away) {
+  uint64_t b;
+  std::memcpy(&b, &v, 8);
+  b &= ~(1ull << 63);
+  int64_t h = (int64_t)(b >> 42) - (1008 << 10);
+  h += away & ((b & ((1ull << 42) - 1)) != 0);
+  h = h >= 0x400 ? h : (away & (b != 0) ? 0x400 : 0);
+  return (uint32_t)std::min<int64_t>(h, away ? 0x7C00 : 0x7BFF);
 }
-uint16_t half_below(double v) {
-  if (v == 0.0) return 0x8000;
-  if (v > 65504.0) return std::isinf(v) ? 0x7C00 : 0x7BFF;
-  int e;
-  std::frexp(v, &e);
-  if (e - 1 < -14) return 0;
-  return (uint16_t)(((e + 14) << 10) | ((uint32_t)std::floor(std::ldexp(v, 11 - e)) - 1024));
-}
-uint16_t half_floor(double v) { return v >= 0 ? half_below(v) : (uint16_t)(0x8000 | half_up(-v)); }
-uint16_t half_ceil(double v) { return v >= 0 ? half_up(v) : (uint16_t)(0x8000 | half_below(-v)); }
+inline uint32_t half_floor(double v) { return v < 0 ? 0x8000u | half_of(v, true) : half_of(v, false); }
+inline uint32_t half_ceil(double v) { return v < 0 ? 0x8000u | half_of(v, false) : half_of(v, true); }
 
 }  // namespace
 
@@ -323,10 +315,9 @@ void pack_nodes(const BvhResult &bvh, PackedNodes &out) {
     uint32_t *w = &out.words[12 * i];
     double org[3];
     for (int a = 0; a < 3; ++a) {
-      double lo = INFINITY, hi = -INFINITY;
-      for (int k : kAxis[a])
-        if (std::isfinite(p[k])) { lo = std::min(lo, (double)p[k]); hi = std::max(hi, (double)p[k]); }
-      const float o = lo <= hi ? (float)(0.5 * (lo + hi) * S) : 0.f;
+      float lo = std::min(p[kAxis[a][0]], p[kAxis[a][2]]), hi = std::max(p[kAxis[a][1]], p[kAxis[a][3]]);
+      if (lo > hi) lo = hi = 0.f;   // (both children empty)
+      const float o = (float)((0.5 * lo + 0.5 * hi) * S);
       std::memcpy(&w[a], &o, 4);
       org[a] = o;
     }
@@ -334,7 +325,7 @@ void pack_nodes(const BvhResult &bvh, PackedNodes &out) {
     for (int c = 0; c < 2; ++c)
       for (int a = 0; a < 3; ++a) {
         const double lo = p[kAxis[a][2 * c]] * S - org[a] - margin, hi = p[kAxis[a][2 * c + 1]] * S - org[a] + margin;
-        w[4 + 3 * c + a] = (uint32_t)half_floor(lo) | (uint32_t)half_ceil(hi) << 16;
+        w[4 + 3 * c + a] = half_floor(lo) | half_ceil(hi) << 16;
       }
     std::memcpy(&w[10], &p[13], 4);
   }
