@@ -526,7 +526,7 @@ def two_stage(hpt, steps, warmup):
     assert torch.isfinite(stack).all().item()
     n_paths = nc * W * H * job["spp"]
     px, py = 4096, 4096
-    moved = nc * T * 8 * (8 * H * px + 2 * H * W)          # bytes the five passes move
+    moved = nc * T * 8 * (4 * H * px + 2 * H * W)          # bytes the three passes move
     out = {"two_stage": {
         "workload": "1920x1080 RGB T=24, ~1M triangles within 5 mm of the recording plane, 256 spp, "
                     "6 bounces, split phase, radiance cache; ASM 80 mm (4096^2 padded)",
@@ -537,9 +537,9 @@ def two_stage(hpt, steps, warmup):
         "asm_GBps_algorithmic": round(nc * T * 16 * H * W * steps / ta / 1e9, 1),
         "focal_stack": "5 planes 80-85 mm behind the hologram, pupil NA 0.02, mean intensity of 24 frames",
         "ms_focal_stack": round(1e3 * tr / steps, 2),
-        # complex64 moved per frame: row spectra once (H W + 3 H Px), then per
-        # plane the column pass, the transpose back and the intensity rows (5 H Px)
-        "focal_stack_GBps_moved": round(nc * T * 8 * H * (W + 3 * px + 5 * px * len(planes)) * steps / tr / 1e9,
+        # complex64 moved per frame: row spectra once, read once by the column
+        # pass (H W + 2 H Px), then per plane its columns and the intensity rows (2 H Px)
+        "focal_stack_GBps_moved": round(nc * T * 8 * H * (W + 2 * px + 2 * px * len(planes)) * steps / tr / 1e9,
                                         1),
         "encoding": "%d Adam steps per field, 72 fields, supervised 82.5 mm behind the hologram" % enc_steps,
         "ms_encoding": round(1e3 * te / steps, 2),
