@@ -27,14 +27,16 @@
 // workgroups of two columns run on a CU, one's memory beside the other's
 // arithmetic; one of four in plain order had all its waves wait together.
 // What bounds the passes, 24 fields of 1920 x 1080 (4096 x 4096 padded): the
-// column pass by vector issue and LDS (51 us a field; 60 with one workgroup of
+// column pass by vector issue (74 %) and LDS (51 us a field; 60 with one workgroup of
 // four columns, 96 with transposes of 12 us each beside it), the row passes by
 // memory (13 and 11 us a field for 52 MB; 11 and 9 in plain order, 26 while their
 // twiddles were gathers). All together 1.74 ms (1.93 in plain order); phase
-// encoding of 1920 x 1080, whose fields exceed the last-level cache, 80 ms (94).
+// encoding of 1920 x 1080, whose fields exceed the last-level cache, 80 ms (94). The
+// transfer function's table in tiles too: 1.69 and, with other steps, 78.8 -> 76.1
+// ms, a focal stack of five planes 6.76 -> 6.15 (it is read once per plane).
 // Tiles of 4 and 16 columns 82 and 84 ms. With short columns the plain order is as
 // fast or faster (1080 x 200: 0.19 ms, tiled 0.20), and so are several planes in
-// workgroups of four (focal stack 6.8 ms, of two 8.3: each plane's transfer
+// workgroups of four (focal stack 6.15 ms, of two 8.1: each plane's transfer
 // function is read in 16-byte pieces).
 #include <hip/hip_runtime.h>
 
@@ -51,14 +53,26 @@ namespace {
 using namespace fft;
 
 // The transfer function's table T[ky][kx] = H at |f_x| = kx / (Px d), |f_y| = ky /
-// (Py d), kx < nx = Px/2 + 1, ky < ny = Py/2 + 1.
+// (Py d), kx < nx = Px/2 + 1, ky < ny = Py/2 + 1. Its first `tiles` groups of
+// kTile columns lie one after the other like the row spectra's (none in plain
+// order), what is left of the columns behind them.
 struct TransferTable {
   float2 *T;
-  uint32_t nx, ny;
+  uint32_t nx, ny, tiles;
   AsmParams P;
   __device__ __forceinline__ void fill(uint32_t i) const {
     if (i >= nx * ny) return;
-    const uint32_t ky = i / nx, kx = i - ky * nx;
+    const uint32_t tiled = tiles * ny * kTile;
+    uint32_t ky, kx;
+    if (i < tiled) {
+      const uint32_t j = i / kTile, tile = j / ny;
+      ky = j - tile * ny;
+      kx = tile * kTile + i % kTile;
+    } else {
+      const uint32_t rest = nx - tiles * kTile;
+      ky = (i - tiled) / rest;
+      kx = tiles * kTile + (i - tiled) - ky * rest;
+    }
     const double fx = (double)kx * P.dfx, fy = (double)ky * P.dfy;
     const double f2 = fx * fx + fy * fy;
     float2 v = make_float2(0.f, 0.f);
@@ -148,8 +162,13 @@ __global__ void __launch_bounds__((Cols<LG, PLANES>::W), (Cols<LG, PLANES>::kWav
   const uint32_t col = xcd_group(blockIdx.x, gridDim.x) * C + c, kx = col < px ? col : 0u;
   const uint32_t h_store = col < px ? h : 0u;
   C2 *x = lds + c;
-  const uint32_t hw = px / 2 + 1, hx = kx <= px / 2 ? kx : px - kx;
-  const size_t plane = (size_t)hw * (L::N / 2 + 1);
+  const uint32_t hw = px / 2 + 1, hx = kx <= px / 2 ? kx : px - kx, ny = L::N / 2 + 1;
+  const size_t plane = (size_t)hw * ny;
+  // this column in the transfer function's tables (see TransferTable): bytes of
+  // its first element and between two rows
+  const uint32_t tiled = (1u << tile_lg) < px ? hw / kTile * kTile : 0u;
+  const uint32_t h_step = (hx < tiled ? kTile : hw - tiled) * 8;
+  const uint32_t h_first = hx < tiled ? (hx / kTile * ny * kTile + hx % kTile) * 8 : (tiled * ny + hx - tiled) * 8;
   const size_t field = (size_t)h * px;
   // element (row t + q TPL, column kx) of a field: q steps from a uniform
   // base, plus one byte offset (below 2^32: h <= 4096, px <= 8192)
@@ -158,11 +177,12 @@ __global__ void __launch_bounds__((Cols<LG, PLANES>::W), (Cols<LG, PLANES>::kWav
   const uint32_t off = ((((kx >> tile_lg) * h + t) << tile_lg) + (kx & ((1u << tile_lg) - 1u))) * 8;
   auto load_h = [&](C2 (&Hr)[E], const float2 *T) {
     // frequency row i = t + q TPL: |f_y| is i steps, from q = E/2 on N - i
-    const uint32_t up = (t * hw + hx) * 8, down = ((L::TPL - 1 - t) * hw + hx) * 8;
+    // (opaque: sixteen offsets kept over the planes would be sixteen registers)
+    uint32_t step_h = h_step, up = h_first + t * h_step, down = h_first + (L::N - t) * h_step;
+    asm volatile("" : "+v"(step_h), "+v"(up), "+v"(down));
 #pragma unroll
     for (uint32_t q = 0; q < E; ++q) {
-      const float2 g = q < E / 2 ? at(T + (size_t)q * L::TPL * hw, up)
-                                 : at(T + (size_t)(L::N - q * L::TPL - (L::TPL - 1)) * hw, down);
+      const float2 g = at(T, q < E / 2 ? up + q * L::TPL * step_h : down - q * L::TPL * step_h);
       Hr[q] = c2(g.x, g.y);
     }
   };
@@ -371,7 +391,8 @@ size_t asm_transfer_elems(uint32_t w, uint32_t h) {
 bool asm_tiled(uint32_t w, uint32_t h) { return asm_padded(h) >= 2048 && asm_padded(w) >= 1u << kTiledLg; }
 
 static TransferTable transfer_table(float2 *T, uint32_t w, uint32_t h, const AsmParams &P) {
-  return {T, asm_padded(w) / 2 + 1, asm_padded(h) / 2 + 1, P};
+  const uint32_t nx = asm_padded(w) / 2 + 1;
+  return {T, nx, asm_padded(h) / 2 + 1, asm_tiled(w, h) ? nx / kTile : 0u, P};
 }
 
 hipError_t launch_asm_transfer(float2 *T, uint32_t w, uint32_t h, const AsmParams &P, hipStream_t st) {
