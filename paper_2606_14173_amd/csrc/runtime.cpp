@@ -109,6 +109,7 @@ struct Job {
   std::vector<Unit> units;
   size_t next = 0, done = 0;
   uint32_t in_flight = 0;     // units in the batch the GPU may still be running
+  bool settled = false;       // its set-up (admit) is known to be through: the job may end
   JobState state = JS_QUEUED;
   hpt_status status = HPT_OK;
   std::string err;
@@ -412,9 +413,11 @@ hpt_status admit(hpt_ctx *C, Job *J) {
   if (e == hipSuccess && J->contrib) e = hipMemsetAsync(J->contrib, 0, J->n_contrib * sizeof(float2), C->stream);
   if (e == hipSuccess && J->sigsum)
     e = hipMemsetAsync(J->sigsum, 0, J->n_sig * sizeof(unsigned long long), C->stream);
-  // (J->host stays as it is until the job is released: no wait for the copy)
+  // (no wait here: a job ends only once its set-up is through, so J->host and
+  // the caller's field outlast it; see Job::settled)
   if (e == hipSuccess) e = hipMemcpyAsync(J->dev, &J->host, sizeof(JobDev), hipMemcpyHostToDevice, C->stream);
   if (e != hipSuccess) {
+    (void)hipStreamSynchronize(C->stream);  // what is already queued of it
     free_job_buffers(C, J);
     return fail(HPT_EDEVICE, std::string("job set-up failed: ") + hipGetErrorString(e));
   }
@@ -625,7 +628,11 @@ hpt_status finish_batch(hpt_ctx *C, int si, double &gpu_ms, uint64_t &rays, hpt_
     t.launches++;
     t.total_ms += m;
   }
-  if (e != hipSuccess) return fail(HPT_EDEVICE, std::string("batch failed: ") + hipGetErrorString(e));
+  if (e != hipSuccess) {
+    (void)hipStreamSynchronize(C->stream);
+    (void)hipStreamSynchronize(C->acc);
+    return fail(HPT_EDEVICE, std::string("batch failed: ") + hipGetErrorString(e));
+  }
   const uint32_t nr = L.h_cnt[2];
   if (L.profile >= 2) { work[0] = L.h_work[0]; work[1] = L.h_work[1]; }
   kt[HPT_K_RAYGEN].items += L.profile ? L.paths : 0;
@@ -668,6 +675,7 @@ void account_batch(hpt_ctx *C, int si, hpt_status s, const std::string &err, dou
     if (std::find(seen.begin(), seen.end(), J) != seen.end()) continue;
     seen.push_back(J);
     J->stats.batches++;
+    J->settled = true;   // its set-up lies before the batch on one stream, and the batch was waited for
     if (J->state != JS_RUNNING) continue;
     if (s != HPT_OK) {
       // the job stops at its next batch boundary; a batch in the other slot
@@ -702,10 +710,21 @@ void scheduler(hpt_ctx *C) {
     });
     if (C->stop && inflight < 0) break;
     // cancellations at the batch boundary; a job with units in flight is
-    // retired once its batch has finished
+    // retired once its batch has finished, one that was in no batch yet once
+    // its set-up is through (it may wait for the caller's stream, and then
+    // clears the caller's field)
+    std::vector<Job *> unsettled;
+    for (Job *J : C->running)
+      if (J->cancel && J->in_flight == 0 && !J->settled) unsettled.push_back(J);
+    if (!unsettled.empty()) {
+      lk.unlock();
+      (void)hipStreamSynchronize(C->stream);
+      lk.lock();
+      for (Job *J : unsettled) J->settled = true;
+    }
     for (size_t k = 0; k < C->running.size();) {
       Job *J = C->running[k];
-      if (J->cancel && J->in_flight == 0) {
+      if (J->cancel && J->in_flight == 0 && J->settled) {
         if (J->fail_status != HPT_OK) retire(C, J, JS_FAILED, J->fail_status, J->fail_err);
         else retire(C, J, JS_CANCELED, HPT_ECANCELED, "cancelled");
       } else {
@@ -751,6 +770,7 @@ void scheduler(hpt_ctx *C) {
         if (inject) C->fail_batches--;
         lk.unlock();
         if (inject) {
+          (void)hipStreamSynchronize(C->stream);  // as launch_batch does when it fails: the set-ups
           L.acc_pending = false;
           L.launch_status = fail(HPT_EDEVICE, "batch launch failed (injected)");
         } else {
@@ -776,6 +796,7 @@ void scheduler(hpt_ctx *C) {
     inflight = launched;
   }
   // drain: everything still queued or running is cancelled
+  (void)hipStreamSynchronize(C->stream);  // set-ups of jobs that were in no batch
   for (Job *J : C->queue) {
     J->state = JS_CANCELED; J->status = HPT_ECANCELED;
     if (J->scene) J->scene->users--;
