@@ -1566,15 +1566,19 @@ uint64_t scratch_room(hpt_ctx *C, uint64_t least) {
   if (room() < least) make_room(C, least);
   return room();
 }
-// A buffer of at least `bytes`: the idle one if it is large enough.
+// A buffer of at least `bytes`: the idle one if it is large enough, but where
+// half of the budget is in use only if it is no more than an eighth too large:
+// what a small call holds of a large buffer cannot be given up for another
+// call or a job that would fit beside it.
 bool scratch_take(hpt_ctx *C, size_t bytes, hpt_ctx::Scratch &S) {
-  if (C->idle.bytes >= bytes) {
+  const bool tight = C->used > C->budget / 2;
+  if (C->idle.bytes >= bytes && (!tight || C->idle.bytes - bytes <= bytes / 8)) {
     S = C->idle;
     C->idle = hpt_ctx::Scratch{};
     S.at = 0;
     return true;
   }
-  C->drop_idle();
+  if (C->idle.bytes < bytes || C->used + bytes > C->budget) C->drop_idle();
   if (C->alloc((void **)&S.p, bytes) != hipSuccess) return false;
   S.bytes = bytes;
   return true;
