@@ -7,6 +7,11 @@ namespace hpt {
 
 constexpr uint32_t kBvhDepthMax = 64;   // traversal stack entries
 constexpr uint32_t kBvhTopNodes = 320;  // nodes stored first, in breadth-first order from the root
+// Least direction component of the slab tests: its reciprocal times a coordinate
+// is finite up to 1e20 (1e-30 lost rays along the axes beyond 3e8), and times
+// the margin of a packed box, 2^-21 of the largest coordinate, still 4e11
+// times that coordinate, farther than any ray is followed.
+constexpr float kSlabMin = 1e-18f;
 
 struct BvhResult {
   std::vector<float> nodes;   // 16 floats per node

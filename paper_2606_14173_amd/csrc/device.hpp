@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "bvh_build.hpp"
 #include "hpt_types.hpp"
 
 namespace hpt {
@@ -131,7 +132,8 @@ __device__ __forceinline__ RayPre ray_pre(F3 o, F3 d, float scale) {
   // good to an ulp, is within the slack of box2)
   const float is = 1.0f / scale;  // exact: a power of two
   auto slab = [&](float c) {
-    return __builtin_amdgcn_fmed3f(__builtin_amdgcn_rcpf(fabsf(c) > 1e-30f ? c : copysignf(1e-30f, c)) * is, -1e36f, 1e36f);
+    const float bounded = fabsf(c) > kSlabMin ? c : copysignf(kSlabMin, c);
+    return __builtin_amdgcn_fmed3f(__builtin_amdgcn_rcpf(bounded) * is, -1e36f, 1e36f);
   };
   r.inv = f3(slab(d.x), slab(d.y), slab(d.z));
   return r;
