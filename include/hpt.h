@@ -239,7 +239,8 @@ hpt_status hpt_field_device_ptr(hpt_ctx *ctx, uint64_t job, void **d_out);
 hpt_status hpt_paths_read(hpt_ctx *ctx, uint64_t job, hpt_path_record *host_out, size_t n);
 hpt_status hpt_contrib_read(hpt_ctx *ctx, uint64_t job, float *host_out, size_t n_floats);
 hpt_status hpt_sigsum_read(hpt_ctx *ctx, uint64_t job, uint64_t *host_out, size_t n);
-/* Remove a queued job or stop a running one at its next batch boundary. */
+/* Remove a queued job or stop a running one at its next batch boundary. Once
+ * hpt_job_wait has reported it, nothing of the job writes d_field any more. */
 hpt_status hpt_job_cancel(hpt_ctx *ctx, uint64_t job);
 /* Free the job's library-owned memory (its field too, unless caller-owned). */
 hpt_status hpt_job_release(hpt_ctx *ctx, uint64_t job);

@@ -27,17 +27,17 @@
 // workgroups of two columns run on a CU, one's memory beside the other's
 // arithmetic; one of four in plain order had all its waves wait together.
 // What bounds the passes, 24 fields of 1920 x 1080 (4096 x 4096 padded): the
-// column pass by vector issue (74 %) and LDS (51 us a field; 60 with one workgroup of
-// four columns, 96 with transposes of 12 us each beside it), the row passes by
-// memory (13 and 11 us a field for 52 MB; 11 and 9 in plain order, 26 while their
-// twiddles were gathers). All together 1.74 ms (1.93 in plain order); phase
-// encoding of 1920 x 1080, whose fields exceed the last-level cache, 80 ms (94). The
-// transfer function's table in tiles too: 1.69 and, with other steps, 78.8 -> 76.1
-// ms, a focal stack of five planes 6.76 -> 6.15 (it is read once per plane).
-// Tiles of 4 and 16 columns 82 and 84 ms. With short columns the plain order is as
-// fast or faster (1080 x 200: 0.19 ms, tiled 0.20), and so are several planes in
-// workgroups of four (focal stack 6.15 ms, of two 8.1: each plane's transfer
-// function is read in 16-byte pieces).
+// column pass by vector issue (80 % of the cycles; 46 us a field, 60 with one
+// workgroup of four columns, 96 with transposes of 12 us each beside it), the row
+// passes by memory (13 and 11 us a field for 52 MB; 11 and 9 in plain order, 26
+// while their twiddles were gathered). All together 1.56 ms, in plain order 1.71;
+// phase encoding of 1920 x 1080, whose fields exceed the last-level cache, 76.1 ms,
+// in plain order 94.8 (tiles of 4 and 16 columns 82 and 84 where 8 took 80); a focal
+// stack of five planes of 24 fields 6.17 ms, in plain order 6.93, of which 0.6 by the
+// transfer functions' tables (one reading a plane). With short columns the plain
+// order is as fast or faster (w x h = 1080 x 200: 0.19 ms, tiled 0.20). Several planes
+// in workgroups of two 8.1 ms: each plane's transfer function is then read in
+// 16-byte pieces. One workgroup of four a CU issues for 60 % of the cycles.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

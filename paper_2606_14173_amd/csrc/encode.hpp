@@ -29,10 +29,9 @@ hipError_t launch_enc_scale(const float2 *A, float2 *R, const float2 *V, double 
 // A = row spectra of R_f - s[f] V_f.
 hipError_t launch_enc_rows_residual(const float2 *R, const float2 *V, const double2 *s, float2 *A, const float2 *tw,
                                     uint32_t nf, uint32_t w, uint32_t h, hipStream_t st);
-// G = the inverse row transforms of A, g = 2 Im(G conj(exp(i phi))), Adam, and the
-// row spectra of the new exp(i phi) -> A; Adam
-// step with bias corrections bc1 = 1 - beta1^k, bc2 = 1 - beta2^k (first: the
-// moments are zero before it).
+// G = the inverse row transforms of A; g = 2 Im(G conj(exp(i phi))); one Adam step
+// with bias corrections bc1 = 1 - beta1^k, bc2 = 1 - beta2^k (first: the moments
+// are zero before it); then the row spectra of the new exp(i phi) -> A.
 hipError_t launch_enc_adam(float2 *A, float *phi, float *m, float *v, const float2 *tw, uint32_t nf, uint32_t w,
                            uint32_t h, float lr, float bc1, float bc2, bool first, hipStream_t st);
 

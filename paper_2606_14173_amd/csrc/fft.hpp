@@ -62,9 +62,11 @@ __device__ __forceinline__ void dft4(C2 &a0, C2 &a1, C2 &a2, C2 &a3, bool inv) {
 // for each n2, twiddles exp(-+2 pi i n2 k1 / 16), DFT-4 over n2; output k =
 // k1 + 4 k2 lands in a[k]. HALF: a[8..15] are zero (a zero-padded line's
 // first stage) and are not read. XR: the inner twiddles m whose imaginary
-// part rounds x sin (as mul_tw does) rather than y cos; the stages differ in
-// it so that propagated fields, and the phases that many Adam steps make of
-// them, keep every bit they had when the compiler chose.
+// part rounds x sin (as mul_tw does) rather than y cos: which product a compiler
+// once rounded first, kept because Adam's steps amplify a last bit. With mul_tw
+// for all, fields are as exact (2.1e-7 of the RMS from 64 bits either way) and as
+// fast, but the phases after 20 steps differ by 6e-6 (300 x 200) and 4e-5
+// (1920 x 1080) of their RMS, to either side of the exact ones.
 template <bool HALF, uint32_t XR>
 __device__ __forceinline__ void dft16(C2 (&a)[16], bool inv) {
   // exp(-2 pi i m / 16), m = 0..9

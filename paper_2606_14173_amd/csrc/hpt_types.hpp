@@ -36,8 +36,9 @@ constexpr uint32_t kTraceChunkMin = 2;             // of a short queue (mix of s
 #endif
 constexpr uint32_t kTraceGridMax = HPT_TRACE_GRID;  // traversal workgroups per launch (8 per CU)
 // A wave's descent stops waiting for the last half of its rays. Of a share of 3/8,
-// 7/16, 1/2, 9/16 and 5/8 a 1920x1080 RGB T = 24 hologram takes 618, 615, 612, 618
-// and 623 ms, a 512x512 one 22.75, 22.7, 22.67, 23.0 and 23.4. (24 lanes whether or
+// 7/16, 1/2, 9/16 and 5/8 a 1920x1080 RGB T = 24 hologram (1M triangles, scene of
+// seed 5; the scenes of seeds 2 and 7 take 698 ms where it takes 613) takes 618, 615,
+// 612, 618 and 623 ms, a 512x512 one 22.75, 22.7, 22.67, 23.0 and 23.4. (24 lanes whether or
 // not the wave had all its rays: 622 and 22.8; 300x200 with direct light 3.76 ms,
 // now 3.54; a mix of six requests 6.54, now 6.22, both of which end in short queues.)
 constexpr int kTraceStragglers = 2;
@@ -45,7 +46,7 @@ constexpr int kTraceStragglers = 2;
 #define HPT_REFILL 16
 #endif
 // idle lanes a traversal wave waits for before it takes new rays: 1 / 8 / 16 /
-// 24 / 32 take 630 / 629 / 625 / 629 / 633 ms for a 1920x1080 RGB T = 24
+// 24 / 32 take 630 / 629 / 625 / 629 / 633 ms for the same 1920x1080 RGB T = 24
 // hologram, 23.1 / 23.1 / 23.0 / 23.2 / 23.5 for a 512x512 one
 constexpr int kTraceRefill = HPT_REFILL;
 #ifndef HPT_CLAIM_CLASSES
@@ -186,11 +187,12 @@ struct RayQueue {
   float4 *ray;                     // 2 per entry: (o, tmin), (d, exclude id bits), traversal input
   float *t;                        // hit distance
   int32_t *prim;                   // leaf-order primitive index of the hit, -1: none
-  // A queue filled by shading is compacted per 256-entry chunk of the
-  // source queue (entries [256 c, 256 c + cnt[c]) hold rays); off holds the
-  // exclusive prefix sums of cnt and idx the entries in order (idx[v] = the
-  // entry of ray v), which the next traversal and shading passes read. The
-  // first queue (ray generation) is dense and read without idx.
+  // The first queue (ray generation) is dense and read without idx, and so are
+  // all queues of a batch with BatchDev::dense. Else a queue filled by shading is
+  // compacted per 256-entry chunk of the source queue (entries [256 c, 256 c +
+  // cnt[c]) hold rays); off holds the exclusive prefix sums of cnt and idx the
+  // entries in order (idx[v] = the entry of ray v), which the next traversal and
+  // shading passes read.
   uint32_t *idx, *cnt, *off;
   uint32_t *tile_sum;              // totals of the counts per tile of 4096 chunks (at most 64)
 };

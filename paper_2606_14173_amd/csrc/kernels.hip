@@ -7,9 +7,13 @@
 //                   coherent delta prefix (FP64 or split OPL), the image
 //                   point (s6-s7) and the incoherent radiance tail; shading
 //                   compacts the live rays of each 256-entry chunk into the
-//                   next queue (ballots, no atomics)
-//   k_scan/k_index  order the chunks of the next queue (prefix sums of the
-//                   chunk counts, then the index list the next pass reads)
+//                   next queue (ballots; a batch of at most kDensePaths paths
+//                   also takes a chunk's place there with one atomic, which
+//                   leaves the queue dense and its order to chance: results
+//                   are kept per path slot and do not depend on it)
+//   k_scan/k_index  order the chunks of a larger batch's next queue (prefix
+//                   sums of the chunk counts, then the index list the next
+//                   pass reads)
 //   k_accumulate    s8-s9: Eq. 5 for all T frames of every path (Path Reuse)
 //   k_points        exact terms of point emitters, after the accumulation
 // Random-phase tables (Eq. 4) are built by k_grf_* once per grid/T/seed.
@@ -534,8 +538,9 @@ __device__ __forceinline__ Bvh shared_bvh_of(const SceneDev &S) {
 
 // ------------------------------------------------------------------ trace
 // FP32 closest hit for every ray of queue q (rays in order: entries 0..n-1
-// of the dense first queue, else the entries idx lists). The queue is cut into chunks of
-// kTraceChunk entries; chunk j belongs to class j mod kClaimClasses, and the
+// of a dense queue, else the entries idx lists). The queue is cut into chunks of
+// kTraceChunk entries, of fewer (down to kTraceChunkMin) where that would leave
+// waves without any; chunk j belongs to class j mod kClaimClasses, and the
 // waves of workgroups with blockIdx mod kClaimClasses = c claim the chunks of
 // class c one at a time from that class's counter (zeroed by the shading pass
 // of the previous use of the queue), so the claim atomics are spread over
@@ -549,12 +554,17 @@ __device__ __forceinline__ Bvh shared_bvh_of(const SceneDev &S) {
 // node-fetch latency than six. ONE: every ray of the batch traverses
 // B.scene_uniform, whose BVH is then held in scalar registers (in vector ones
 // six were spilled) and its first nodes in LDS.
-// Bound by vector instructions (85 % of the cycles) and by vector-L1 accesses
-// (89 %, one per lane and load, half of the lanes): 48-byte nodes for 64-byte
-// ones, and a third fewer instructions per node, took the 1M-triangle scene's
-// 1920x1080 RGB T = 24 hologram from 691 to 635 ms and its 512x512 one from
-// 25.6 to 23.4 ms. (A mixed batch's top nodes, shared out in LDS, gained it
-// nothing.)
+// COUNT keeps two counters a lane, for which 72 VGPRs are too few (up to ten
+// spilled), so it runs at six waves.
+// Bound by vector instructions and vector-L1 accesses (one per lane and load):
+// 93 and 82 % of the cycles in a 512x512 RGB hologram of the 58k-triangle scene,
+// 58 % of the lanes; in a 1920x1080 one of the 1M-triangle scene 83 % and 59 %
+// of the lanes. Incoherent rays wait for the caches instead (a 64^3 x 8^2 bake:
+// 50 and 55 %, L2 hit 74 %). 48-byte nodes for 64-byte ones, and a third fewer
+// instructions per node, took the 1920x1080 RGB T = 24 hologram from 691 to
+// 635 ms (scene of seed 5; of seed 2 it takes 14 % longer) and the 512x512 one
+// from 25.6 to 23.4 ms. (A mixed batch's top nodes, shared out in LDS, gained
+// it nothing.)
 template <bool COUNT, bool ONE, bool NEE>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(COUNT ? 6 : 7)))
     k_trace(BatchDev B, int q, int dense) {
@@ -905,8 +915,6 @@ __device__ __forceinline__ void image_point(const BatchDev &B, const RayQueue &Q
   }
 }
 
-// One interaction of the incoherent tail at x (index b), reached along d_in
-// on primitive gid. Returns a ray to trace in `e`, or finishes the path.
 // Next-event estimate at the non-delta tail vertex x (material m, primitive
 // gid, reached along d_in): an emitter triangle chosen with probability
 // proportional to area, a point uniform on it; its unoccluded one-sided
@@ -947,6 +955,9 @@ __device__ __forceinline__ LightSample next_event(const SceneDev &S, const Mater
   return s;
 }
 
+// One interaction of the incoherent tail at x (index b), reached along d_in
+// on the primitive of H. Returns a ray to trace in `e` (EXT: with the occlusion
+// query of its light sample in Sh), or finishes the path.
 template <bool EXT>
 __device__ __forceinline__ void tail_interaction(const BatchDev &B, const RayQueue &Q, StageLds &G,
                                                  const UnitDev &U, const JobDev &J, const SceneDev &S,
@@ -1639,7 +1650,7 @@ __global__ void __launch_bounds__(kPtsBlock) k_points(BatchDev B) {
 // rounded to binary16. It runs beside the next batch's traversal, which it
 // takes memory accesses from: 4 bytes a path, one after the other, instead of a
 // 32-byte record each (and the same in finish()) took the bake of 3 x 16.8 M
-// entries of 4 paths from 121.2 to 118.7 ms. The unit of the workgroup's first
+// entries of 4 paths from 121.2 to 118.7 ms (scene of seed 5). The unit of the workgroup's first
 // entry comes from scalar loads; its other entries lie there or in the next
 // ones.
 __global__ void __launch_bounds__(kBlock) k_cache_reduce(BatchDev B) {

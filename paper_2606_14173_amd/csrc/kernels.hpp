@@ -6,15 +6,16 @@
 
 namespace hpt {
 
-// uni: the batch has one job and at most shade_lds_units() units
 // Whether a batch of n_paths keeps dense queues (BatchDev::dense).
 bool dense_queues(uint32_t n_paths);
+// uni: the batch has one job and at most shade_lds_units() units
 hipError_t launch_raygen(const BatchDev &B, bool uni, hipStream_t st);
 // One interaction for every ray in queue q: closest hit (trace), then
 // shading that compacts continuing rays into queue q^1 (shade).
 // Fails (hipErrorInvalidValue) if the batch's stack spill is too small.
-// dense: queue q is the first queue (ray generation order), else it is read
-// through its index list.
+// dense: queue q holds rays 0..n-1 (the first queue, and all of a batch with
+// dense queues), else it is read through its index list. nee: its tail entries
+// may hold occlusion queries.
 hipError_t launch_trace(const BatchDev &B, int q, bool dense, bool count, bool nee, hipStream_t st);
 // After the shading pass over queue q: prefix sums of the per-chunk counts
 // of queue q^1, its ray count and its index list.
@@ -23,10 +24,10 @@ hipError_t launch_compact(const BatchDev &B, int q, hipStream_t st);
 // n_paths (they size the stack spill).
 uint32_t trace_grid(uint32_t n_paths);
 uint32_t trace_block();
-// first: queue from k_raygen; ext: the batch's jobs use next-event estimation
+// ext: the batch's jobs use next-event estimation
 // or principled materials (extended shading kernel); uni: the batch has one
-// job, at most shade_lds_mats() materials and at most shade_lds_units() units
-// shading pass `pass` (0: the first, over ray generation's queue)
+// job, at most shade_lds_mats() materials and at most shade_lds_units() units;
+// pass: 0 is the first, over ray generation's queue.
 hipError_t launch_shade(const BatchDev &B, int q, uint32_t pass, bool ext, bool uni, hipStream_t st);
 uint32_t shade_lds_mats();
 uint32_t shade_lds_units();

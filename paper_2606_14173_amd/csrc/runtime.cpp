@@ -1548,10 +1548,14 @@ hpt_status hpt_grf_read(hpt_ctx *C, uint32_t gw, uint32_t gh, uint32_t T, uint64
 constexpr uint32_t kMaxFieldsPerLaunch = 65535;
 constexpr uint32_t kEncBuffers = 11;  // buffers the encoding takes of its scratch (256-byte boundaries)
 // Work buffers of a call: fields are taken in chunks of at most this much.
-// Propagation: four 1080p fields, whose row spectra the memory-side cache
-// holds between the passes (24 of them: 1.90 ms; in chunks of 256 MiB 2.00,
-// of 1 GiB 1.95). Encoding: 512 MiB, where a launch still has six fields to
-// spread over the CUs (150 MiB, one field: 121 ms instead of 94). Focal
+// Propagation: 160 MiB, four fields of 1920 x 1080, whose row spectra the
+// memory-side cache holds between the passes. Chunks of 70, 105, 160, 205, 275
+// and 1024 MiB: 24 of those fields 1.78, 1.62, 1.56, 1.59, 1.60 and 1.56 ms, 96
+// of 512 x 1080 1.71, 1.61, 1.56, 1.62, 1.71 and 1.72, 64 of 512 x 512 0.38, 0.36,
+// 0.34, 0.37, 0.41 and 0.41; 8 of 3840 x 2160, 135 MiB each, 4.00 ms one at a time
+// (up to 205 MiB), 3.62 at 275 and 3.34 at 1024 MiB: fields so large would gain
+// from larger chunks. Encoding: 512 MiB, where a launch still has six
+// fields to spread over the CUs (150 MiB, one field: 98 ms instead of 76). Focal
 // stacks: planes times frames.
 constexpr uint64_t kAsmChunkBytes = 160ull << 20, kEncChunkBytes = 512ull << 20, kStackChunkBytes = 1ull << 30;
 
