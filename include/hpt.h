@@ -280,9 +280,10 @@ hpt_status hpt_ctx_stats_get(hpt_ctx *ctx, hpt_ctx_stats *out);
  * field's, and a quarter of the transfer function) is taken from the context's
  * budget for the call. EINVAL on bad arguments, EBUDGET if one field's scratch
  * does not fit, EDEVICE on a HIP error.
- * The scratch of the last such call (or reconstruction or encoding) stays
- * allocated for the next one and counts as used; it is freed as soon as a
- * scene, cache, table or job needs its room, and by hpt_destroy. */
+ * The scratch of the last such calls (and reconstructions and encodings; at
+ * most four, 1 GiB together) stays allocated for the next ones of their sizes
+ * and counts as used; it is freed as soon as a call, scene, cache, table or job
+ * needs its room, and by hpt_destroy. */
 #define HPT_ASM_BAND_LIMIT 1u
 hpt_status hpt_asm_propagate(hpt_ctx *ctx, const void *d_in, void *d_out, uint32_t n_fields,
                              uint32_t width, uint32_t height, double pitch, double lambda,

@@ -206,10 +206,11 @@ struct hpt_ctx {
   hpt_kernel_time ktime[HPT_K_KINDS] = {};
   uint64_t node_visits = 0, prim_tests = 0;
 
-  // Work buffer of a finished propagation, reconstruction or encoding, kept
-  // for the next one (counted in `used`): at most one, given up when anything
-  // else needs its room. Allocating it anew took a 24 x 1080p propagation of
-  // 2.4 ms between 0.3 and 25 ms.
+  // Work buffers of finished propagations, reconstructions and encodings, kept
+  // for the next ones of their sizes (counted in `used`; the last used one
+  // last): at most kIdleKept, together at most kIdleBytes, given up when
+  // anything else needs their room. Allocating one anew took a 24 x 1080p
+  // propagation of 2.4 ms between 0.3 and 25 ms.
   struct Scratch {
     char *p = nullptr;
     size_t bytes = 0, at = 0;
@@ -219,15 +220,20 @@ struct hpt_ctx {
       at += (n * sizeof(T) + 255) / 256 * 256;
       return r;
     }
-  } idle;
-
+  };
+  std::vector<Scratch> idle;
+  uint64_t idle_bytes() const {
+    uint64_t n = 0;
+    for (const Scratch &s : idle) n += s.bytes;
+    return n;
+  }
   void drop_idle() {
-    release(idle.p, idle.bytes);
-    idle = Scratch{};
+    for (const Scratch &s : idle) release(s.p, s.bytes);
+    idle.clear();
   }
   hipError_t alloc(void **p, size_t bytes) {
     hipError_t e = hipMalloc(p, bytes ? bytes : 16);
-    if (e != hipSuccess && idle.p) {
+    if (e != hipSuccess && !idle.empty()) {
       (void)hipGetLastError();
       drop_idle();
       e = hipMalloc(p, bytes ? bytes : 16);
@@ -268,7 +274,7 @@ uint64_t passband_bins(uint32_t gw, uint32_t gh) {
   return n;
 }
 
-// Drop the idle work buffer, then tables no running job uses, until `need`
+// Drop the idle work buffers, then tables no running job uses, until `need`
 // more bytes fit the budget.
 void make_room(hpt_ctx *C, size_t need) {
   if (C->used + need > C->budget) C->drop_idle();
@@ -938,7 +944,7 @@ void hpt_destroy(hpt_ctx *C) {
   (void)hipStreamSynchronize(C->acc);
   for (auto &kv : C->jobs) free_job_buffers(C, kv.second.get());
   for (auto &g : C->grfs) (void)hipFree(g->d);
-  if (C->idle.p) (void)hipFree(C->idle.p);
+  for (auto &s : C->idle) (void)hipFree(s.p);
   for (JobDev *p : C->job_devs) (void)hipFree(p);
   for (auto &kv : C->scenes) {
     for (void *p : kv.second->bufs) (void)hipFree(p);
@@ -1558,39 +1564,45 @@ constexpr uint32_t kEncBuffers = 11;  // buffers the encoding takes of its scrat
 // fields to spread over the CUs (150 MiB, one field: 98 ms instead of 76). Focal
 // stacks: planes times frames.
 constexpr uint64_t kAsmChunkBytes = 160ull << 20, kEncChunkBytes = 512ull << 20, kStackChunkBytes = 1ull << 30;
+constexpr size_t kIdleKept = 4;                          // work buffers a context keeps,
+constexpr uint64_t kIdleBytes = kStackChunkBytes;        // no more than its largest call took
 
 namespace {
 // Work buffers (lock held). scratch_room: bytes a call may take, after making
-// room for `least`; the idle buffer counts as free.
+// room for `least`; the idle buffers count as free.
 uint64_t scratch_room(hpt_ctx *C, uint64_t least) {
   auto room = [&] {
-    const uint64_t used = C->used - std::min<uint64_t>(C->used, C->idle.bytes);
+    const uint64_t used = C->used - std::min<uint64_t>(C->used, C->idle_bytes());
     return C->budget > used ? C->budget - used : 0;
   };
   if (room() < least) make_room(C, least);
   return room();
 }
-// A buffer of at least `bytes`: the idle one if it is large enough, but where
-// half of the budget is in use only if it is no more than an eighth too large:
-// what a small call holds of a large buffer cannot be given up for another
-// call or a job that would fit beside it.
+// A buffer of at least `bytes`: the smallest idle one that is at most an eighth
+// larger, else a new one. (What a call holds cannot be given up for another call
+// or a job, so a small call must not hold a large buffer.)
 bool scratch_take(hpt_ctx *C, size_t bytes, hpt_ctx::Scratch &S) {
-  const bool tight = C->used > C->budget / 2;
-  if (C->idle.bytes >= bytes && (!tight || C->idle.bytes - bytes <= bytes / 8)) {
-    S = C->idle;
-    C->idle = hpt_ctx::Scratch{};
+  auto best = C->idle.end();
+  for (auto i = C->idle.begin(); i != C->idle.end(); ++i)
+    if (i->bytes >= bytes && i->bytes - bytes <= bytes / 8 && (best == C->idle.end() || i->bytes < best->bytes)) best = i;
+  if (best != C->idle.end()) {
+    S = *best;
     S.at = 0;
+    C->idle.erase(best);
     return true;
   }
-  if (C->idle.bytes < bytes || C->used + bytes > C->budget) C->drop_idle();
+  if (C->used + bytes > C->budget) C->drop_idle();
   if (C->alloc((void **)&S.p, bytes) != hipSuccess) return false;
   S.bytes = bytes;
   return true;
 }
-// Give S back once nothing uses it: the larger of it and the idle buffer stays.
-void scratch_give(hpt_ctx *C, hpt_ctx::Scratch &S) {
-  if (S.bytes > C->idle.bytes) std::swap(S, C->idle);
-  C->release(S.p, S.bytes);
+// Give S back once nothing uses it: it stays, and the longest unused go.
+void scratch_give(hpt_ctx *C, const hpt_ctx::Scratch &S) {
+  C->idle.push_back(S);
+  while (C->idle.size() > kIdleKept || C->idle_bytes() > kIdleBytes) {
+    C->release(C->idle.front().p, C->idle.front().bytes);
+    C->idle.erase(C->idle.begin());
+  }
 }
 
 // Order the work about to be enqueued on `work` after everything enqueued on

@@ -114,6 +114,28 @@ def test_job_beside_a_small_call():
         assert np.isfinite(U).all() and np.abs(U).max() > 0
 
 
+def test_job_that_takes_the_rest_of_an_ample_budget():
+    """Less than half of the budget is in use, but the job's table and scratch
+    (24 bytes a point and frame) leave 30 MB of it."""
+    import paper_2606_14173_amd as hpt
+    with hpt.Context(0, 64 << 20) as c:
+        used = c.ctx_stats()["used_bytes"]
+    room = used + (192 << 20)
+    side = int(np.sqrt((room - (30 << 20)) / (24 * 8)))
+    assert side <= 4096
+    j = dict(jobs.JOB_DEFAULTS)
+    j.update(width=64, height=64, lambdas=[LAM], comps=[1], spp=4, max_bounces=2, T=8, seed=1, grf_seed=7, grf_w=side,
+             grf_h=side, phase_mode=jobs.PHASE_SPLIT)
+    with hpt.Context(0, used + room) as c:
+        sid = c.upload_scene(scenes.scene_tiny(0))
+        before, left = _leave_large_buffer(c)
+        assert left > 30 << 20 and 2 * (before + left) <= used + room
+        small = _SmallCall(c)
+        U = c.trace(sid, j)
+        small.end()
+        assert np.isfinite(U).all() and np.abs(U).max() > 0
+
+
 def test_buffer_is_given_up():
     """Nothing of it is lost to the budget's count when its room is needed."""
     with _context() as c:
